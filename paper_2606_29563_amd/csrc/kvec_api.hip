@@ -4,6 +4,7 @@
 #include <string.h>
 
 #include "kvec_internal.h"
+#include "kvec_select_dev.h"
 
 namespace kvec {
 
@@ -108,10 +109,8 @@ kvec_status make_geometry(const kvec_config* c, Geometry* g) {
   x.esize = c->dtype == KVEC_BF16 ? 2 : 4;
   const int64_t chunks = (int64_t)H * x.B * (x.D * x.esize / 16);
   x.n_gather = (int)((chunks + 4 * kThreads - 1) / (4 * kThreads));
-  // selection task LDS: 2048-bin histogram, 32 ints, member offsets, then
-  // four 4-byte arrays per member
-  const size_t sel_fixed = 2048 * 4 + 32 * 4 + (size_t)((x.n_prep + 1 + 3) & ~3) * 4;
-  x.mcap = (int)(((kLdsMax - kLdsStatic - sel_fixed) / 16) & ~(size_t)63);
+  // selection task LDS: a fixed part, then three 4-byte arrays per member
+  x.mcap = (int)(((kLdsMax - kLdsStatic - select_fixed_lds(x.n_prep)) / 12) & ~(size_t)63);
   g->keep_all = x.T <= x.B;
   return KVEC_OK;
 }
@@ -130,8 +129,10 @@ Workspace make_workspace(const Geometry& g) {
   // one ring slot
   w.lse_part = take(bt * P.HQ * P.Wn * P.n_kt1 * 8);
   w.lse2 = take(bt * P.HQ * P.Wn * 4);
-  w.psum_base = take(bt * P.n_rt * P.H * tc * 4);
+  // without mixed row tiles the last-O sums of a base tile are its sums over
+  // all its rows: one array
   w.psum_all = take(bt * P.n_rt * P.H * tc * 4);
+  w.psum_base = P.nsum == 2 ? take(bt * P.n_rt * P.H * tc * 4) : w.psum_all;
   w.ipart = take(bt * P.n_rt * tc * 4);
   w.imp = take(bt * tc * 4);
   w.pooled = take(bt * P.H * tc * 4);
@@ -147,7 +148,7 @@ Workspace make_workspace(const Geometry& g) {
   w.counts_stride = align256(bt * P.T);
   w.counts = take(2 * w.counts_stride);
   w.spill_stride = align256(bt * P.H * tc * 4);
-  w.spill = take(4 * w.spill_stride);
+  w.spill = take(3 * w.spill_stride);
   w.total = off;
   // dynamic LDS: the largest task
   const int tpw = 8 / P.H;
@@ -156,8 +157,7 @@ Workspace make_workspace(const Geometry& g) {
   const size_t lds_p2 = key_ring_bytes(P.esize, P.D) + (p2_all > p2_ext ? p2_all : p2_ext) * 4;
   const size_t lds_pool = (size_t)(2 * (kPoolPer * kPoolChunk + 64) + 2 * kHistBins) * 4 + kPoolPer * 16;
   const size_t lds_prep = 256;
-  const size_t lds_sel = 2048 * 4 + 32 * 4 + (size_t)((P.n_prep + 1 + 3) & ~3) * 4 +
-                         (size_t)16 * P.mcap;
+  const size_t lds_sel = select_fixed_lds(P.n_prep) + (size_t)12 * P.mcap;
   size_t lds = lds_p2;
   if (lds_pool > lds) lds = lds_pool;
   if (lds_prep > lds) lds = lds_prep;

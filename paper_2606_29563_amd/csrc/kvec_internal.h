@@ -90,7 +90,7 @@ struct Workspace {
       mem_ps, mem_i, mem_n;
   size_t slot_bytes;
   size_t counts, counts_stride;  // two uint8 [b][T] count buffers (layer parity)
-  size_t spill, spill_stride;    // four [b][H][Tc] member arrays
+  size_t spill, spill_stride;    // three [b][H][Tc] member arrays
   size_t lds_bytes;
   size_t total;
 };
@@ -169,37 +169,36 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
-// Inclusive prefix sum over the 64 lanes of a wave.
+// Inclusive prefix sum over the 64 lanes of a wave: DPP row shifts within the
+// rows of 16 lanes, then the row broadcasts (vector instructions only).
 __device__ __forceinline__ int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(v, o);
-    if (lane >= o) v += u;
-  }
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2, 3
   return v;
 }
 
-// Exclusive prefix sum over the work-group (blockDim.x a multiple of 64, at
-// most 1024).  `tmp` holds >= 17 ints of shared memory.  Returns the
-// exclusive prefix; `total` receives the block sum.  Contains barriers.
+// Exclusive prefix sum over a work-group of kThreads (8 waves).  `tmp` holds
+// 8 ints of shared memory.  Returns the exclusive prefix; `total` receives the
+// block sum.  Contains barriers (tmp is free again on return).
 __device__ __forceinline__ int block_excl_scan(int v, int* tmp, int& total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int nw = blockDim.x >> 6;
   const int incl = wave_incl_scan(v);
   if (lane == 63) tmp[wid] = incl;
   __syncthreads();
-  if (wid == 0) {
-    const int x = lane < nw ? tmp[lane] : 0;
-    const int xi = wave_incl_scan(x);
-    if (lane < nw) tmp[lane] = xi - x;
-    if (lane == nw - 1) tmp[16] = xi;
+  int before = 0;
+  total = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const int x = tmp[w];
+    before += w < wid ? x : 0;
+    total += x;
   }
   __syncthreads();
-  const int r = tmp[wid] + incl - v;
-  total = tmp[16];
-  __syncthreads();
-  return r;
+  return before + incl - v;
 }
 
 // Pool work-groups per (sequence, head): each writes one float64 (sum, sum

@@ -258,7 +258,7 @@ struct ScoreIO {
   float* lse2;        // [b][HQ][Wn]
   const float* lse_in;  // nullable: caller's natural-log normalisers, rows contiguous
   int64_t lse_b, lse_h;
-  float* psum_base;   // [b][n_rt][H][Tc]
+  float* psum_base;   // [b][n_rt][H][Tc] (psum_all itself when no row tile is mixed)
   float* psum_all;    // [b][n_rt][H][Tc]
   float* ipart;       // [b][n_rt][Tc]
 };
@@ -780,7 +780,7 @@ struct ScoreTile {
           const int t = ks + i;
           if (t < P.Tc) {
             io.psum_all[o + t] = obuf[(hs * P.nsum) * P.tile2 + i];
-            io.psum_base[o + t] = obuf[(hs * P.nsum + P.nsum - 1) * P.tile2 + i];
+            if (P.nsum == 2) io.psum_base[o + t] = obuf[(hs * 2 + 1) * P.tile2 + i];
           }
         }
         if (tile_base && hs == 0) {

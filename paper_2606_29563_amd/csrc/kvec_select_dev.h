@@ -61,7 +61,6 @@ struct SelectIO {
   float* out_imp;          // and I [b][Tc]
   uint32_t* spill_keys;    // [b][H][Tc] member arrays when members exceed the LDS capacity
   int32_t* spill_t;
-  float* spill_ps;
   float* spill_i;
   const uint8_t* cnt_in;   // [b][T] counts of earlier layers (null: none)
   const uint64_t* bits_prev; // bitmap row of the previous layer, [b] stride L*W (null: none)
@@ -329,86 +328,75 @@ __device__ __forceinline__ void task_prep(const Problem& P, const SelectIO& io, 
 // select: one work-group per (layer, sequence, head)
 // ---------------------------------------------------------------------------
 
+// LDS of the selection tasks before the members: three radix histograms, scan
+// scratch and the member offsets of the prep chunks.
+constexpr int kRadixBins = 2048 + 2048 + 1024;
+__host__ __device__ inline size_t select_fixed_lds(int n_prep) {
+  return (size_t)kRadixBins * 4 + 32 * 4 + (size_t)((n_prep + 1 + 3) & ~3) * 4;
+}
+
 // Block radix select over keys k[0..n) (512 threads): the first `want` keys in
 // the order (key desc, index asc) are those > thr plus the first `take` keys
-// equal to thr.  Three passes of 11, 11 and 10 bits over an LDS histogram.
+// equal to thr.  Three passes of 11, 11 and 10 bits, each over its own LDS
+// histogram (all cleared first, so a pass takes three barriers); `tmp` holds
+// 10 ints.
 __device__ __forceinline__ void block_radix_select(const uint32_t* kb, int n, int want,
                                                    uint32_t* hist, int* tmp, uint32_t& thr,
                                                    int& take) {
   uint32_t prefix = 0, mask = 0;
   int rem = want;
-  const int shifts[3] = {21, 10, 0};
-  const int widths[3] = {11, 11, 10};
+  for (int i = threadIdx.x; i < kRadixBins; i += kThreads) hist[i] = 0u;
+  __syncthreads();
 #pragma unroll
   for (int ps = 0; ps < 3; ++ps) {
-    const int shift = shifts[ps], nb = 1 << widths[ps];
+    const int shift = ps == 0 ? 21 : ps == 1 ? 10 : 0;
+    constexpr int kWide = 2048 / kThreads, kNarrow = 1024 / kThreads;
+    const int nb = ps == 2 ? 1024 : 2048, per = ps == 2 ? kNarrow : kWide;
     const uint32_t dm = (uint32_t)nb - 1u;
-    for (int i = threadIdx.x; i < nb; i += blockDim.x) hist[i] = 0u;
-    __syncthreads();
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    uint32_t* hp = hist + ps * 2048;
+    for (int i = threadIdx.x; i < n; i += kThreads) {
       const uint32_t kk = kb[i];
-      if ((kk & mask) == prefix) atomicAdd(&hist[(kk >> shift) & dm], 1u);
+      if ((kk & mask) == prefix) atomicAdd(&hp[(kk >> shift) & dm], 1u);
     }
     __syncthreads();
     // descending order: thread owns bins nb-1-tid*per .. nb-per-tid*per
-    const int per = nb / (int)blockDim.x;
-    int cnt[4] = {0, 0, 0, 0}, sum = 0;
+    int cnt[kWide], sum = 0;
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < kWide; ++e) {
+      cnt[e] = 0;
       if (e < per) {
-        cnt[e] = (int)hist[nb - 1 - ((int)threadIdx.x * per + e)];
+        cnt[e] = (int)hp[nb - 1 - ((int)threadIdx.x * per + e)];
         sum += cnt[e];
       }
-    int total;
-    const int before = block_excl_scan(sum, tmp, total);
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int incl = wave_incl_scan(sum);
+    if (lane == 63) tmp[wid] = incl;
+    __syncthreads();
+    int before = incl - sum;
+#pragma unroll
+    for (int w = 0; w < kThreads / 64; ++w) before += w < wid ? tmp[w] : 0;
     if (before < rem && rem <= before + sum) {
       int run = before;
       bool found = false;
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < kWide; ++e)
         if (e < per && !found && run + cnt[e] >= rem) {
-          tmp[20] = nb - 1 - ((int)threadIdx.x * per + e);
-          tmp[21] = rem - run;
+          tmp[8] = nb - 1 - ((int)threadIdx.x * per + e);
+          tmp[9] = rem - run;
           found = true;
         } else if (e < per) {
           run += cnt[e];
         }
     }
     __syncthreads();
-    prefix |= (uint32_t)tmp[20] << shift;
+    prefix |= (uint32_t)tmp[8] << shift;
     mask |= dm << shift;
-    rem = tmp[21];
-    __syncthreads();
+    rem = tmp[9];
   }
+  __syncthreads();
   thr = prefix;
   take = rem;
-}
-
-// Flags of the first `want` members (given thr/take from the radix select),
-// in member order, by a blocked prefix count of the keys equal to thr.
-// Calls fn(i, selected) for every member i of this thread's block range.
-template <class Fn>
-__device__ __forceinline__ void block_flags(const uint32_t* kb, int n, int want, uint32_t thr,
-                                            int take, int* tmp, Fn fn) {
-  const int per = (n + blockDim.x - 1) / blockDim.x;
-  const int lo = min(n, (int)threadIdx.x * per), hi = min(n, lo + per);
-  int ceq = 0;
-  for (int i = lo; i < hi; ++i) ceq += kb[i] == thr;
-  int total;
-  int e = block_excl_scan(ceq, tmp, total);
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t kk = kb[i];
-    bool sel;
-    if (want >= n) {
-      sel = true;
-    } else if (want <= 0) {
-      sel = false;
-    } else {
-      sel = kk > thr || (kk == thr && e < take);
-      e += kk == thr;
-    }
-    fn(i, sel);
-  }
 }
 
 // The selection of a layer runs as two tasks one launch apart, both one
@@ -416,17 +404,100 @@ __device__ __forceinline__ void block_flags(const uint32_t* kb, int n, int want,
 // layer's bitmap row (n_t), so the first runs while that row is still being
 // written, which halves the serial chain from layer to layer.
 //
+// Both are chains of global round trips and LDS passes of one work-group, and
+// set the length of a launch whose score tiles are short.  So: every global
+// load is issued in batches, member arrays are reached through pointers known
+// to be LDS (SPILL: the rare list longer than the LDS capacity stays in global
+// memory, in its own copy of the code), and stores are coalesced.
+//
 // select A: gathers the head's candidate members (contiguous, ascending t),
 // takes the preserve set (first Kp by P_sel desc, t asc) and writes the
 // members back compacted into the head's member arrays: t (bitwise
 // complemented for preserved members), P_sel, I; their count goes to
 // mem_n[.][h][0].
+constexpr int kSelBatch = 8;
+
+template <bool SPILL>
+__device__ __forceinline__ void select_a_members(const Problem& P, const SelectIO& io, int64_t hb, int n,
+                                                 char* smem) {
+  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
+  int* tmp = reinterpret_cast<int*>(hist + kRadixBins);    // [32]
+  int* off = tmp + 32;                                     // [n_prep + 1] member offsets
+  uint32_t* kb = reinterpret_cast<uint32_t*>(smem + select_fixed_lds(P.n_prep));
+  int32_t* mt = reinterpret_cast<int32_t*>(kb + P.mcap);
+  float* mi = reinterpret_cast<float*>(mt + P.mcap);
+  if constexpr (SPILL) {
+    kb = io.spill_keys + hb * P.Tc;
+    mt = io.spill_t + hb * P.Tc;
+    mi = io.spill_i + hb * P.Tc;
+  }
+  // gather the members contiguously (ascending t); the key holds P_sel
+  int32_t* gt = io.mem_t + hb * P.Tc;
+  float* gp = io.mem_ps + hb * P.Tc;
+  float* gi = io.mem_i + hb * P.Tc;
+  for (int i0 = threadIdx.x; i0 < n; i0 += kSelBatch * kThreads) {
+    int g[kSelBatch];  // member position in the head's chunk arrays
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int i = min(i0 + u * kThreads, n - 1);
+      int lo = 0, hi = P.n_prep - 1;  // chunk c with off[c] <= i < off[c+1]
+      while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= i) lo = mid; else hi = mid - 1;
+      }
+      g[u] = lo * kPrepChunk + (i - off[lo]);
+    }
+    int32_t vt[kSelBatch];
+    float vp[kSelBatch], vi[kSelBatch];
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      vt[u] = gt[g[u]];
+      vp[u] = gp[g[u]];
+      vi[u] = gi[g[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int i = i0 + u * kThreads;
+      if (i < n) {
+        mt[i] = vt[u];
+        mi[i] = vi[u];
+        kb[i] = float_key(vp[u]);
+      }
+    }
+  }
+  __syncthreads();
+  // preserve set: first Kp members by (P_sel desc, t asc), marked by ~t
+  const int kp = min(P.Kp, n);
+  if (kp > 0) {
+    uint32_t thr = 0u;
+    int take = 0, eq0 = 0;
+    const int per = (n + kThreads - 1) / kThreads;
+    const int lo = min(n, (int)threadIdx.x * per), hi = min(n, lo + per);
+    if (kp < n) {
+      block_radix_select(kb, n, kp, hist, tmp, thr, take);
+      int ceq = 0, total;
+      for (int i = lo; i < hi; ++i) ceq += kb[i] == thr;
+      eq0 = block_excl_scan(ceq, tmp, total);
+    }
+    for (int i = lo; i < hi; ++i) {
+      const uint32_t kk = kb[i];
+      const bool eq = kk == thr;
+      if (kp >= n || kk > thr || (eq && eq0 < take)) mt[i] = ~mt[i];
+      eq0 += eq;
+    }
+    __syncthreads();
+  }
+  // write the members back compacted (every chunk-layout read is done)
+  for (int i = threadIdx.x; i < n; i += kThreads) {
+    gt[i] = mt[i];
+    gp[i] = key_float(kb[i]);
+    gi[i] = mi[i];
+  }
+}
+
 __device__ __forceinline__ void task_select_a(const Problem& P, const SelectIO& io, int b, int h,
                                               char* smem) {
-  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);    // [2048]
-  int* tmp = reinterpret_cast<int*>(hist + 2048);          // [32]
-  int* off = tmp + 32;                                     // [n_prep + 1] member offsets
-  char* marr = reinterpret_cast<char*>(off + ((P.n_prep + 1 + 3) & ~3));
+  int* off = reinterpret_cast<int*>(smem) + kRadixBins + 32;
   const int64_t hb = (int64_t)b * P.H + h;
   int32_t* mn = io.mem_n + hb * P.n_prep;
   // member offsets of the prep chunks (wave 0, 64 chunks per round)
@@ -444,71 +515,10 @@ __device__ __forceinline__ void task_select_a(const Problem& P, const SelectIO& 
   }
   __syncthreads();
   const int n = off[P.n_prep];
-  uint32_t* kb;
-  int32_t* mt;
-  float *mp, *mi;
-  if (n <= P.mcap) {
-    kb = reinterpret_cast<uint32_t*>(marr);
-    mt = reinterpret_cast<int32_t*>(kb + P.mcap);
-    mp = reinterpret_cast<float*>(mt + P.mcap);
-    mi = mp + P.mcap;
-  } else {
-    kb = io.spill_keys + hb * P.Tc;
-    mt = io.spill_t + hb * P.Tc;
-    mp = io.spill_ps + hb * P.Tc;
-    mi = io.spill_i + hb * P.Tc;
-  }
-  // gather the members contiguously (ascending t), with their preserve keys;
-  // kBatch members per thread have their loads in flight together
-  constexpr int kBatch = 8;
-  int32_t* gt = io.mem_t + hb * P.Tc;
-  float* gp = io.mem_ps + hb * P.Tc;
-  float* gi = io.mem_i + hb * P.Tc;
-  for (int i0 = threadIdx.x; i0 < n; i0 += kBatch * blockDim.x) {
-    int g[kBatch];  // member position in the head's chunk arrays
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = i0 + u * (int)blockDim.x;
-      int lo = 0, hi = P.n_prep - 1;  // chunk c with off[c] <= i < off[c+1]
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (off[mid] <= i) lo = mid; else hi = mid - 1;
-      }
-      g[u] = lo * kPrepChunk + (i - off[lo]);
-    }
-    int32_t vt[kBatch];
-    float vp[kBatch], vi[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const bool ok = i0 + u * (int)blockDim.x < n;
-      vt[u] = ok ? gt[g[u]] : 0;
-      vp[u] = ok ? gp[g[u]] : 0.f;
-      vi[u] = ok ? gi[g[u]] : 0.f;
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = i0 + u * (int)blockDim.x;
-      if (i < n) {
-        mt[i] = vt[u];
-        mp[i] = vp[u];
-        mi[i] = vi[u];
-        kb[i] = float_key(vp[u]);
-      }
-    }
-  }
-  __syncthreads();
-  // preserve set: first Kp members by (P_sel desc, t asc)
-  const int kp = min(P.Kp, n);
-  uint32_t thr_p = 0xffffffffu;
-  int take_p = 0;
-  if (kp > 0 && kp < n) block_radix_select(kb, n, kp, hist, tmp, thr_p, take_p);
-  // write the members back compacted (every chunk-layout read is done: the
-  // gather ended with a barrier), preserved ones marked by ~t
-  block_flags(kb, n, kp, thr_p, take_p, tmp, [&](int i, bool pres) {
-    gt[i] = pres ? ~mt[i] : mt[i];
-    gp[i] = mp[i];
-    gi[i] = mi[i];
-  });
+  if (n <= P.mcap)
+    select_a_members<false>(P, io, hb, n, smem);
+  else
+    select_a_members<true>(P, io, hb, n, smem);
   if (threadIdx.x == 0) mn[0] = n;
 }
 
@@ -516,79 +526,60 @@ __device__ __forceinline__ void task_select_a(const Problem& P, const SelectIO& 
 // preserve set, else P_sel + lambda * I * (1 - n_t/(l+1)) in fp32 op by op),
 // the final pick of the first B-O by (P' desc, t asc), its emission in
 // ascending order with the window, and the layer's bitmap row.
-__device__ __forceinline__ void task_select_b(const Problem& P, const SelectIO& io, int layer, int b,
-                                              int h, char* smem) {
-  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);    // [2048]
-  int* tmp = reinterpret_cast<int*>(hist + 2048);          // [32]
-  char* marr = reinterpret_cast<char*>(tmp + 32 + ((P.n_prep + 1 + 3) & ~3));
+template <bool SPILL>
+__device__ __forceinline__ void select_b_members(const Problem& P, const SelectIO& io, int layer, int b,
+                                                 int h, int n, char* smem) {
+  uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
+  int* tmp = reinterpret_cast<int*>(hist + kRadixBins);    // [32]
   const int64_t hb = (int64_t)b * P.H + h;
-  const int n = io.mem_n[hb * P.n_prep];
   const int32_t* gt = io.mem_t + hb * P.Tc;
   const float* gp = io.mem_ps + hb * P.Tc;
   const float* gi = io.mem_i + hb * P.Tc;
-  uint32_t* kb;
-  const int32_t* mt;
-  const float *mp, *mi;
-  if (n <= P.mcap) {
-    kb = reinterpret_cast<uint32_t*>(marr);
-    int32_t* lt = reinterpret_cast<int32_t*>(kb + P.mcap);
-    float* lp = reinterpret_cast<float*>(lt + P.mcap);
-    float* li = lp + P.mcap;
-    // members into LDS, kBatch loads per thread in flight together
-    constexpr int kBatch = 8;
-    for (int i0 = threadIdx.x; i0 < n; i0 += kBatch * blockDim.x) {
-      int32_t vt[kBatch];
-      float vp[kBatch], vi[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = min(i0 + u * (int)blockDim.x, n - 1);
-        vt[u] = gt[i];
-        vp[u] = gp[i];
-        vi[u] = gi[i];
-      }
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = i0 + u * (int)blockDim.x;
-        if (i < n) {
-          lt[i] = vt[u];
-          lp[i] = vp[u];
-          li[i] = vi[u];
-        }
-      }
-    }
-    __syncthreads();
-    mt = lt;
-    mp = lp;
-    mi = li;
-  } else {
-    // long member lists stay in global memory; the keys go to this layer's
-    // pooled-score array, free once the candidates were extracted
+  // long member lists stay in global memory; the keys go to this layer's
+  // pooled-score array, free once the candidates were extracted
+  uint32_t* kb = reinterpret_cast<uint32_t*>(smem + select_fixed_lds(P.n_prep));
+  int32_t* lt = reinterpret_cast<int32_t*>(kb + P.mcap);
+  const int32_t* mt = lt;
+  if constexpr (SPILL) {
     kb = reinterpret_cast<uint32_t*>(io.pooled) + hb * P.Tc;
     mt = gt;
-    mp = gp;
-    mi = gi;
   }
   // P' keys: 1.0 on the preserve set, else P_sel + lambda * I * (1 - n_t/(l+1))
   const float f_denom = (float)(layer + 1);
-  const uint8_t* cnt = io.cnt_in;
-  const uint64_t* prow = io.bits_prev;
-  {
-    const int per = (n + blockDim.x - 1) / blockDim.x;
-    const int lo = min(n, (int)threadIdx.x * per), hi = min(n, lo + per);
-    for (int i = lo; i < hi; ++i) {
-      const int te = mt[i];
-      float pp;
-      if (te < 0) {
-        pp = 1.0f;
-      } else {
-        const int t = te;
-        int nt = cnt ? (int)cnt[(int64_t)b * P.T + t] : 0;
-        if (prow) nt += (int)((prow[(int64_t)b * P.L * P.words + (t >> 6)] >> (t & 63)) & 1ull);
-        const float cov = __fdiv_rn((float)nt, f_denom);
-        const float focus = __fmul_rn(mi[i], __fsub_rn(1.0f, cov));
-        pp = __fadd_rn(mp[i], __fmul_rn(P.lam, focus));
+  const uint8_t* cnt = io.cnt_in ? io.cnt_in + (int64_t)b * P.T : nullptr;
+  const uint64_t* prow = io.bits_prev ? io.bits_prev + (int64_t)b * P.L * P.words : nullptr;
+  for (int i0 = threadIdx.x; i0 < n; i0 += kSelBatch * kThreads) {
+    int32_t vt[kSelBatch];
+    float vp[kSelBatch], vi[kSelBatch];
+    int nt[kSelBatch];
+    uint64_t pw[kSelBatch];
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int i = min(i0 + u * kThreads, n - 1);
+      vt[u] = gt[i];
+      vp[u] = gp[i];
+      vi[u] = gi[i];
+    }
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int t = vt[u] < 0 ? ~vt[u] : vt[u];
+      nt[u] = cnt ? (int)cnt[t] : 0;
+      pw[u] = prow ? prow[t >> 6] : 0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < kSelBatch; ++u) {
+      const int i = i0 + u * kThreads;
+      float pp = 1.0f;
+      if (vt[u] >= 0) {
+        const int n_t = nt[u] + (int)((pw[u] >> (vt[u] & 63)) & 1ull);
+        const float cov = __fdiv_rn((float)n_t, f_denom);
+        const float focus = __fmul_rn(vi[u], __fsub_rn(1.0f, cov));
+        pp = __fadd_rn(vp[u], __fmul_rn(P.lam, focus));
       }
-      kb[i] = float_key(pp);
+      if (i < n) {
+        kb[i] = float_key(pp);
+        if constexpr (!SPILL) lt[i] = vt[u];
+      }
     }
   }
   __syncthreads();
@@ -597,35 +588,37 @@ __device__ __forceinline__ void task_select_b(const Problem& P, const SelectIO& 
   uint32_t thr = 0xffffffffu;
   int take = 0;
   if (m > 0 && m < n) block_radix_select(kb, n, m, hist, tmp, thr, take);
-  // output positions: blocked count of the selected members, then emission
-  const int per = (n + blockDim.x - 1) / blockDim.x;
+  // output positions: blocked counts of the members above the cut and at it
+  const int per = (n + kThreads - 1) / kThreads;
   const int lo = min(n, (int)threadIdx.x * per), hi = min(n, lo + per);
-  int ceq = 0;
-  for (int i = lo; i < hi; ++i) ceq += kb[i] == thr;
-  int total;
-  const int e0 = block_excl_scan(ceq, tmp, total);
-  auto selected = [&](uint32_t kk, int& e) {
-    if (m >= n) return true;
-    if (m <= 0) return false;
-    const bool eq = kk == thr;
-    const bool sel = kk > thr || (eq && e < take);
-    e += eq;
-    return sel;
-  };
-  int csel = 0;
-  {
-    int e = e0;
-    for (int i = lo; i < hi; ++i) csel += selected(kb[i], e);
+  int cgt = 0, ceq = 0;
+  if (m > 0) {
+    for (int i = lo; i < hi; ++i) {
+      const uint32_t kk = kb[i];
+      cgt += m >= n || kk > thr;
+      ceq += m < n && kk == thr;
+    }
   }
-  int o = block_excl_scan(csel, tmp, total);
+  int total;
+  const int g0 = block_excl_scan(cgt, tmp, total);
+  int e = m < n ? block_excl_scan(ceq, tmp, total) : 0;
+  // before this thread's first pick: every earlier member above the cut and
+  // the taken ones of the earlier members at it
+  int o = g0 + min(e, take);
   int32_t* out = io.idx + hb * P.B;
   uint64_t* row = io.bits + ((int64_t)b * P.L + layer) * P.words;
   uint64_t word = 0;
   int cur = -1;
-  {
-    int e = e0;
+  if (m > 0) {
     for (int i = lo; i < hi; ++i) {
-      if (!selected(kb[i], e)) continue;
+      const uint32_t kk = kb[i];
+      bool sel = m >= n;
+      if (m < n) {
+        const bool eq = kk == thr;
+        sel = kk > thr || (eq && e < take);
+        e += eq;
+      }
+      if (!sel) continue;
       const int te = mt[i];
       const int t = te < 0 ? ~te : te;
       out[o++] = t;
@@ -638,12 +631,21 @@ __device__ __forceinline__ void task_select_b(const Problem& P, const SelectIO& 
     }
   }
   if (cur >= 0) atomicOr((unsigned long long*)&row[cur], (unsigned long long)word);
-  for (int i = threadIdx.x; i < P.O; i += blockDim.x) out[P.M + i] = P.Tc + i;
+  for (int i = threadIdx.x; i < P.O; i += kThreads) out[P.M + i] = P.Tc + i;
   if (h == 0) {
     // the observation window is always kept
-    for (int t = P.Tc + threadIdx.x; t < P.T; t += blockDim.x)
+    for (int t = P.Tc + threadIdx.x; t < P.T; t += kThreads)
       atomicOr((unsigned long long*)&row[t >> 6], 1ull << (t & 63));
   }
+}
+
+__device__ __forceinline__ void task_select_b(const Problem& P, const SelectIO& io, int layer, int b,
+                                              int h, char* smem) {
+  const int n = io.mem_n[((int64_t)b * P.H + h) * P.n_prep];
+  if (n <= P.mcap)
+    select_b_members<false>(P, io, layer, b, h, n, smem);
+  else
+    select_b_members<true>(P, io, layer, b, h, n, smem);
 }
 
 // Running coverage counts of the pipeline: n_t(layer) = n_t(layer-1) + kept

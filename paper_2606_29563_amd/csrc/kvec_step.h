@@ -106,8 +106,7 @@ __device__ __forceinline__ SelectIO select_io(const StepArgs& a, int layer, int 
   io.out_imp = a.sc_imp ? a.sc_imp + (int64_t)layer * a.P.batch * a.P.Tc : nullptr;
   io.spill_keys = reinterpret_cast<uint32_t*>(a.ws + a.w.spill);
   io.spill_t = reinterpret_cast<int32_t*>(a.ws + a.w.spill + a.w.spill_stride);
-  io.spill_ps = reinterpret_cast<float*>(a.ws + a.w.spill + 2 * a.w.spill_stride);
-  io.spill_i = reinterpret_cast<float*>(a.ws + a.w.spill + 3 * a.w.spill_stride);
+  io.spill_i = reinterpret_cast<float*>(a.ws + a.w.spill + 2 * a.w.spill_stride);
   const uint8_t* cnt = reinterpret_cast<const uint8_t*>(a.ws + a.w.counts);
   if (a.standalone_counts) {
     // counts of the caller's earlier rows, computed for this call
