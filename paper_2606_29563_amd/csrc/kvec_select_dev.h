@@ -68,6 +68,23 @@ struct SelectIO {
   int32_t* idx;            // [b][H][B] of this layer
 };
 
+// Max-pool of the raw scores at tokens t + 64 k (k < kPoolLane), window 2 r + 1
+// truncated to [0, Tc): the clamped end tokens only repeat a member of the
+// window.  The loop runs over the window, so that a wave has the reads of all
+// its tokens in flight (token by token, each read waited for the one before).
+constexpr int kPoolLane = kPoolChunk / 64;
+__device__ __forceinline__ void pool_max(const float* raw, int t, int r, int Tc, float (&m)[kPoolLane]) {
+#pragma unroll
+  for (int k = 0; k < kPoolLane; ++k) m[k] = raw[min(t + 64 * k, Tc - 1)];
+  for (int d = 1; d <= r; ++d) {
+#pragma unroll
+    for (int k = 0; k < kPoolLane; ++k) {
+      const int u = min(t + 64 * k, Tc - 1);
+      m[k] = fmaxf(fmaxf(m[k], raw[max(u - d, 0)]), raw[min(u + d, Tc - 1)]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // pool: grid item (b, h, chunk); 512 threads.  want_p: pool P (with the sigma
 // sums, the P histogram and, for head 0, I); want_e: pool P over O' (and its
@@ -90,7 +107,10 @@ __device__ __forceinline__ void task_pool(const Problem& P, const SelectIO& io, 
   uint32_t* hp = reinterpret_cast<uint32_t*>(se + (kPoolPer * kPoolChunk + 64));
   uint32_t* he = hp + kHistBins;
   double2* wst = reinterpret_cast<double2*>(he + kHistBins);  // [kPoolPer] chunk sums
-  for (int i = threadIdx.x; i < 2 * kHistBins; i += blockDim.x) hp[i] = 0u;
+  for (int i = threadIdx.x; i < kHistBins; i += kThreads) {
+    if (want_p) hp[i] = 0u;
+    if (want_e) he[i] = 0u;
+  }
   const int64_t row = ((int64_t)b * P.H + h) * P.Tc;
   // The window is at most kPoolPer * kPoolChunk + 62 tokens: kSpan loads per
   // thread, unrolled so that every load of the thread is in flight at once.
@@ -181,30 +201,46 @@ __device__ __forceinline__ void task_pool(const Problem& P, const SelectIO& io, 
   const int chunk = c0 + w;
   if (chunk < c1) {
     const int ct0 = chunk * kPoolChunk, ct1 = min(P.Tc, ct0 + kPoolChunk);
-    double s1 = 0.0, s2 = 0.0;
-    for (int t = ct0 + lane; t < ct1; t += 64) {
-      const int u0 = max(0, t - r), u1 = min(P.Tc - 1, t + r);
-      float m = sp[u0 - a0], me = se[u0 - a0];
-      for (int u = u0 + 1; u <= u1; ++u) {
-        m = fmaxf(m, sp[u - a0]);
-        me = fmaxf(me, se[u - a0]);
-      }
-      if (want_p) {
-        io.pooled[row + t] = m;
-        s1 += (double)m;
-        // sigma: sum of squares; entropy: sum of x ln x (0 ln 0 = 0)
-        s2 += P.criterion ? (m > 0.f ? (double)m * log((double)m) : 0.0) : (double)m * (double)m;
-        atomicAdd(&hp[float_key(m) >> (32 - kHistBits)], 1u);
-      }
-      if (want_e) {
-        io.pooled_ext[row + t] = me;
-        atomicAdd(&he[float_key(me) >> (32 - kHistBits)], 1u);
-      }
-    }
     if (want_p) {
+      float m[kPoolLane];
+      pool_max(sp - a0, ct0 + lane, r, P.Tc, m);
+      double s1 = 0.0, s2 = 0.0;
+#pragma unroll
+      for (int k = 0; k < kPoolLane; ++k) {
+        const int t = ct0 + lane + 64 * k;
+        if (t < ct1) {
+          io.pooled[row + t] = m[k];
+          s1 += (double)m[k];
+          s2 += (double)m[k] * (double)m[k];
+          atomicAdd(&hp[float_key(m[k]) >> (32 - kHistBits)], 1u);
+        }
+      }
+      if (P.criterion) {
+        // entropy: the sum of x ln x (0 ln 0 = 0) in place of the squares, one
+        // token at a time (one copy of the logarithm's code)
+        s2 = 0.0;
+#pragma unroll 1
+        for (int t = ct0 + lane; t < ct1; t += 64) {
+          float x = sp[t - a0];
+          for (int d = 1; d <= r; ++d) x = fmaxf(fmaxf(x, sp[max(t - d, 0) - a0]), sp[min(t + d, P.Tc - 1) - a0]);
+          s2 += x > 0.f ? (double)x * log((double)x) : 0.0;
+        }
+      }
       s1 = wave_sum(s1);
       s2 = wave_sum(s2);
       if (lane == 0) wst[w] = make_double2(s1, s2);
+    }
+    if (want_e) {
+      float m[kPoolLane];
+      pool_max(se - a0, ct0 + lane, r, P.Tc, m);
+#pragma unroll
+      for (int k = 0; k < kPoolLane; ++k) {
+        const int t = ct0 + lane + 64 * k;
+        if (t < ct1) {
+          io.pooled_ext[row + t] = m[k];
+          atomicAdd(&he[float_key(m[k]) >> (32 - kHistBits)], 1u);
+        }
+      }
     }
   }
   __syncthreads();
@@ -218,9 +254,10 @@ __device__ __forceinline__ void task_pool(const Problem& P, const SelectIO& io, 
     io.stats[((int64_t)b * P.H + h) * pool_groups(P) + c0 / kPoolPer] = make_double2(s1, s2);
   }
   uint32_t* gh = io.hist + ((int64_t)b * 2 * P.H) * kHistBins;
-  for (int i = threadIdx.x; i < kHistBins; i += blockDim.x) {
-    if (hp[i]) atomicAdd(&gh[(int64_t)h * kHistBins + i], hp[i]);
-    if (he[i]) atomicAdd(&gh[(int64_t)(P.H + h) * kHistBins + i], he[i]);
+  for (int i = threadIdx.x; i < kHistBins; i += kThreads) {
+    const uint32_t cp = want_p ? hp[i] : 0u, ce = want_e ? he[i] : 0u;
+    if (cp) atomicAdd(&gh[(int64_t)h * kHistBins + i], cp);
+    if (ce) atomicAdd(&gh[(int64_t)(P.H + h) * kHistBins + i], ce);
   }
 }
 
