@@ -45,15 +45,6 @@ namespace {
 
 using namespace step;
 
-__global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
-}
-
-__global__ void counts_kernel(Problem P, const uint64_t* bits, uint8_t* counts, int layer) {
-  task_counts_from_bits(P, bits, counts, layer, blockIdx.y, blockIdx.x);
-}
-
 // P, P over O', I of one layer from the score partials (fixed order).
 __global__ void finalize_kernel(Problem P, const float* psum_base, const float* psum_all,
                                 const float* ipart, float* p_raw, float* p_ext, float* imp) {
@@ -117,8 +108,10 @@ int seg_count(const Problem& P, int st) {
   const bool ext = P.delta_eff > 0;
   switch (st) {
     case ST_SELECT:
-    case ST_SELA: return P.batch * P.H;
+    case ST_SELA:
+    case ST_SELAB: return P.batch * P.H;
     case ST_COUNT: return P.batch * ((P.words + kCountWords - 1) / kCountWords);
+    case ST_CNTB: return P.batch * ((P.words + kBitWords - 1) / kBitWords);
     case ST_PASS1: return P.batch * P.n_kt1 * P.n_rtg;
     case ST_P1B: return P.batch * P.n_kt1 * P.n_rtg_base;
     case ST_P1X: return ext_wgs(P, P.n_kt1);
@@ -200,19 +193,15 @@ void set_seg(StepArgs& a, int st, int v, int n_steps = 1) {
   a.seg[st] = Seg{v % a.P.L, v % kRing, seg_count(a.P, st), v / a.P.L};
 }
 
-hipError_t fill(uint32_t* p, int64_t n, uint32_t v, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-
 // Pass 1, row normalisers and pass 2 of one layer into ring slot 0 (pass 2
-// alone when the caller gives the row normalisers).
-hipError_t score_stages(StepArgs a, const Workspace& w, hipStream_t s) {
+// alone when the caller gives the row normalisers).  count_layer >= 0: the
+// last launch also counts the caller's bitmap rows before that layer.
+hipError_t score_stages(StepArgs a, const Workspace& w, hipStream_t s, int count_layer = -1) {
   const int order[3] = {ST_PASS1, ST_LSE, ST_PASS2};
   for (int i = a.lse ? 2 : 0; i < 3; ++i) {
     for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0};
     a.seg[order[i]] = Seg{0, 0, seg_count(a.P, order[i]), 0};
+    if (i == 2 && count_layer >= 0) a.seg[ST_CNTB] = Seg{count_layer, 0, seg_count(a.P, ST_CNTB), 0};
     const hipError_t e = launch(a, w, s);
     if (e != hipSuccess) return e;
   }
@@ -310,19 +299,12 @@ hipError_t run_score(const Geometry& g, const void* q, const int64_t qs[3], cons
 }
 
 // Selection stages of one layer; scores from the caller (p_raw != null) or
-// from the workspace partials of ring slot 0.
+// from the workspace partials of ring slot 0, whose last launch has counted
+// the earlier layers' bitmap rows.
 static hipError_t select_stages(const Geometry& g, int layer, const float* p_raw, const float* p_ext,
                                 const float* imp, uint64_t* bits, int32_t* idx, uint32_t* htop,
                                 char* ws, const Workspace& w, hipStream_t s) {
   const Problem& P = g.p;
-  hipError_t e;
-  // n_t of this layer from the caller's bitmap rows of the earlier layers
-  hipLaunchKernelGGL(counts_kernel, dim3(P.words, P.batch), dim3(64), 0, s, P, bits,
-                     reinterpret_cast<uint8_t*>(ws + w.counts), layer);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (p_raw && (e = fill(reinterpret_cast<uint32_t*>(ws + w.hist),
-                         (int64_t)P.batch * 2 * P.H * kHistBins, 0u, s)) != hipSuccess)
-    return e;
   StepArgs a = base_args(g, ws, w);
   a.p_raw = p_raw;
   a.p_ext = p_ext;
@@ -331,11 +313,12 @@ static hipError_t select_stages(const Geometry& g, int layer, const float* p_raw
   a.idx = idx;
   a.htop = htop;
   a.standalone_counts = 1;
-  const int order[4] = {ST_POOL, ST_PREP, ST_SELA, ST_SELECT};
-  for (int i = 0; i < 4; ++i) {
+  const int order[4] = {ST_CNTB, ST_POOL, ST_PREP, ST_SELAB};
+  for (int i = p_raw ? 0 : 1; i < 4; ++i) {
     for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0};
     a.seg[order[i]] = Seg{layer, 0, seg_count(P, order[i]), 0};
-    if ((e = launch(a, w, s)) != hipSuccess) return e;
+    const hipError_t e = launch(a, w, s);
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
@@ -356,7 +339,7 @@ hipError_t run_evict_layer(const Geometry& g, int layer, const ModelIO& m, char*
   StepArgs a = base_args(g, ws, w);
   set_model(a, m);
   // scores of this layer into ring slot 0 (the tensors carry no layer dimension)
-  if ((e = score_stages(a, w, s)) != hipSuccess) return e;
+  if ((e = score_stages(a, w, s, layer)) != hipSuccess) return e;
   if ((e = select_stages(g, layer, nullptr, nullptr, nullptr, m.bits, m.idx, nullptr, ws, w, s)) !=
       hipSuccess)
     return e;

@@ -439,7 +439,9 @@ __device__ __forceinline__ void block_radix_select(const uint32_t* kb, int n, in
 // The selection of a layer runs as two tasks one launch apart, both one
 // work-group per (sequence, head).  Only the second needs the previous
 // layer's bitmap row (n_t), so the first runs while that row is still being
-// written, which halves the serial chain from layer to layer.
+// written, which halves the serial chain from layer to layer.  The per-layer
+// entry points, which have no next layer to overlap, run both as one task
+// (SEL_AB): one launch less, and the members stay in LDS in between.
 //
 // Both are chains of global round trips and LDS passes of one work-group, and
 // set the length of a launch whose score tiles are short.  So: every global
@@ -453,10 +455,11 @@ __device__ __forceinline__ void block_radix_select(const uint32_t* kb, int n, in
 // complemented for preserved members), P_sel, I; their count goes to
 // mem_n[.][h][0].
 constexpr int kSelBatch = 8;
+enum SelMode { SEL_A = 1, SEL_B = 2, SEL_AB = 3 };
 
 template <bool SPILL>
 __device__ __forceinline__ void select_a_members(const Problem& P, const SelectIO& io, int64_t hb, int n,
-                                                 char* smem) {
+                                                 char* smem, int mode) {
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
   int* tmp = reinterpret_cast<int*>(hist + kRadixBins);    // [32]
   int* off = tmp + 32;                                     // [n_prep + 1] member offsets
@@ -524,39 +527,14 @@ __device__ __forceinline__ void select_a_members(const Problem& P, const SelectI
     }
     __syncthreads();
   }
-  // write the members back compacted (every chunk-layout read is done)
+  // write the members back compacted (every chunk-layout read is done), unless
+  // select B follows in this task and finds them in LDS
+  if (!SPILL && mode == SEL_AB) return;
   for (int i = threadIdx.x; i < n; i += kThreads) {
     gt[i] = mt[i];
     gp[i] = key_float(kb[i]);
     gi[i] = mi[i];
   }
-}
-
-__device__ __forceinline__ void task_select_a(const Problem& P, const SelectIO& io, int b, int h,
-                                              char* smem) {
-  int* off = reinterpret_cast<int*>(smem) + kRadixBins + 32;
-  const int64_t hb = (int64_t)b * P.H + h;
-  int32_t* mn = io.mem_n + hb * P.n_prep;
-  // member offsets of the prep chunks (wave 0, 64 chunks per round)
-  if (threadIdx.x < 64) {
-    const int lane = threadIdx.x;
-    int carry = 0;
-    for (int c0 = 0; c0 < P.n_prep; c0 += 64) {
-      const int c = c0 + lane;
-      const int v = c < P.n_prep ? mn[c] : 0;
-      const int incl = wave_incl_scan(v);
-      if (c < P.n_prep) off[c] = carry + incl - v;
-      carry += __shfl(incl, 63);
-    }
-    if (lane == 0) off[P.n_prep] = carry;
-  }
-  __syncthreads();
-  const int n = off[P.n_prep];
-  if (n <= P.mcap)
-    select_a_members<false>(P, io, hb, n, smem);
-  else
-    select_a_members<true>(P, io, hb, n, smem);
-  if (threadIdx.x == 0) mn[0] = n;
 }
 
 // select B: the coverage-aware priority P' of every member (1.0 on the
@@ -565,7 +543,7 @@ __device__ __forceinline__ void task_select_a(const Problem& P, const SelectIO& 
 // ascending order with the window, and the layer's bitmap row.
 template <bool SPILL>
 __device__ __forceinline__ void select_b_members(const Problem& P, const SelectIO& io, int layer, int b,
-                                                 int h, int n, char* smem) {
+                                                 int h, int n, char* smem, int mode) {
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem);
   int* tmp = reinterpret_cast<int*>(hist + kRadixBins);    // [32]
   const int64_t hb = (int64_t)b * P.H + h;
@@ -576,6 +554,7 @@ __device__ __forceinline__ void select_b_members(const Problem& P, const SelectI
   // pooled-score array, free once the candidates were extracted
   uint32_t* kb = reinterpret_cast<uint32_t*>(smem + select_fixed_lds(P.n_prep));
   int32_t* lt = reinterpret_cast<int32_t*>(kb + P.mcap);
+  const float* li = reinterpret_cast<const float*>(lt + P.mcap);
   const int32_t* mt = lt;
   if constexpr (SPILL) {
     kb = reinterpret_cast<uint32_t*>(io.pooled) + hb * P.Tc;
@@ -590,12 +569,22 @@ __device__ __forceinline__ void select_b_members(const Problem& P, const SelectI
     float vp[kSelBatch], vi[kSelBatch];
     int nt[kSelBatch];
     uint64_t pw[kSelBatch];
+    if (!SPILL && mode == SEL_AB) {
 #pragma unroll
-    for (int u = 0; u < kSelBatch; ++u) {
-      const int i = min(i0 + u * kThreads, n - 1);
-      vt[u] = gt[i];
-      vp[u] = gp[i];
-      vi[u] = gi[i];
+      for (int u = 0; u < kSelBatch; ++u) {
+        const int i = min(i0 + u * kThreads, n - 1);
+        vt[u] = lt[i];
+        vp[u] = key_float(kb[i]);
+        vi[u] = li[i];
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < kSelBatch; ++u) {
+        const int i = min(i0 + u * kThreads, n - 1);
+        vt[u] = gt[i];
+        vp[u] = gp[i];
+        vi[u] = gi[i];
+      }
     }
 #pragma unroll
     for (int u = 0; u < kSelBatch; ++u) {
@@ -676,13 +665,45 @@ __device__ __forceinline__ void select_b_members(const Problem& P, const SelectI
   }
 }
 
-__device__ __forceinline__ void task_select_b(const Problem& P, const SelectIO& io, int layer, int b,
-                                              int h, char* smem) {
-  const int n = io.mem_n[((int64_t)b * P.H + h) * P.n_prep];
+template <bool SPILL>
+__device__ __forceinline__ void select_members(const Problem& P, const SelectIO& io, int layer, int b, int h,
+                                               int n, char* smem, int mode) {
+  if (mode & SEL_A) {
+    select_a_members<SPILL>(P, io, (int64_t)b * P.H + h, n, smem, mode);
+    if (mode & SEL_B) __syncthreads();
+  }
+  if (mode & SEL_B) select_b_members<SPILL>(P, io, layer, b, h, n, smem, mode);
+}
+
+__device__ __forceinline__ void task_select(const Problem& P, const SelectIO& io, int layer, int b, int h,
+                                            char* smem, int mode) {
+  int* off = reinterpret_cast<int*>(smem) + kRadixBins + 32;
+  int32_t* mn = io.mem_n + ((int64_t)b * P.H + h) * P.n_prep;
+  int n;
+  if (mode & SEL_A) {
+    // member offsets of the prep chunks (wave 0, 64 chunks per round)
+    if (threadIdx.x < 64) {
+      const int lane = threadIdx.x;
+      int carry = 0;
+      for (int c0 = 0; c0 < P.n_prep; c0 += 64) {
+        const int c = c0 + lane;
+        const int v = c < P.n_prep ? mn[c] : 0;
+        const int incl = wave_incl_scan(v);
+        if (c < P.n_prep) off[c] = carry + incl - v;
+        carry += __shfl(incl, 63);
+      }
+      if (lane == 0) off[P.n_prep] = carry;
+    }
+    __syncthreads();
+    n = off[P.n_prep];
+  } else {
+    n = mn[0];  // written by select A
+  }
   if (n <= P.mcap)
-    select_b_members<false>(P, io, layer, b, h, n, smem);
+    select_members<false>(P, io, layer, b, h, n, smem, mode);
   else
-    select_b_members<true>(P, io, layer, b, h, n, smem);
+    select_members<true>(P, io, layer, b, h, n, smem, mode);
+  if (mode == SEL_A && threadIdx.x == 0) mn[0] = n;
 }
 
 // Running coverage counts of the pipeline: n_t(layer) = n_t(layer-1) + kept
@@ -705,15 +726,30 @@ __device__ __forceinline__ void task_count(const Problem& P, const uint8_t* cnt_
   }
 }
 
-// n_t for a standalone layer call: counts of the caller's bitmap rows < layer.
+// n_t for a per-layer call: counts of the caller's bitmap rows < layer.  Part
+// `part` of kBitWords bitmap words, one word per wave and round: its lanes
+// read that word of 64 rows at once, then lane i counts bit i row by row.
+constexpr int kBitWords = 16;
+
 __device__ __forceinline__ void task_counts_from_bits(const Problem& P, const uint64_t* bits,
-                                                      uint8_t* counts, int layer, int b, int wi) {
-  const int tlo = wi * 64;
-  for (int t = tlo + (int)threadIdx.x; t < min(tlo + 64, P.T); t += blockDim.x) {
+                                                      uint8_t* counts, int layer, int b, int part) {
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int k = w; k < kBitWords; k += kThreads / 64) {
+    const int wi = part * kBitWords + k;
+    if (wi >= P.words) break;
     int nt = 0;
-    for (int l = 0; l < layer; ++l)
-      nt += (int)((bits[((int64_t)b * P.L + l) * P.words + wi] >> (t - tlo)) & 1ull);
-    counts[(int64_t)b * P.T + t] = (uint8_t)nt;
+    for (int l0 = 0; l0 < layer; l0 += 64) {
+      const int l = l0 + lane;
+      const uint64_t x = l < layer ? bits[((int64_t)b * P.L + l) * P.words + wi] : 0ull;
+      const int nl = min(64, layer - l0);
+      for (int u = 0; u < nl; ++u) {
+        const uint64_t row = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(x >> 32), u) << 32) |
+                             (uint32_t)__builtin_amdgcn_readlane((int)x, u);
+        nt += (int)((row >> lane) & 1ull);
+      }
+    }
+    const int t = wi * 64 + lane;
+    if (t < P.T) counts[(int64_t)b * P.T + t] = (uint8_t)nt;
   }
 }
 

@@ -14,9 +14,11 @@ namespace step {
 
 // Segments are dispatched in this order (long work-groups first).  *_B and
 // *_X are the last-O and the extended-window halves of the layer pipeline;
-// the plain stages cover every row and head (per-layer entry points).
+// the plain stages cover every row and head (per-layer entry points).  SELAB
+// and CNTB are the whole selection and the counts from the caller's bitmap of
+// a per-layer call.
 enum Stage {
-  ST_SELECT = 0, ST_SELA, ST_COUNT,
+  ST_SELECT = 0, ST_SELA, ST_SELAB, ST_COUNT, ST_CNTB,
   ST_PASS2, ST_P2B, ST_P2X,
   ST_PASS1, ST_P1B, ST_P1X,
   ST_LSE, ST_LSEB, ST_LSEX,
@@ -233,14 +235,24 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     if (blk >= sg.count) return;
   }
   switch (st) {
-    case ST_SELECT: {
+    case ST_SELECT:
+    case ST_SELA:
+    case ST_SELAB: {
       const int b = blk / P.H, h = blk % P.H;
-      task_select_b(P, select_io(a, sg.layer, sg.slot, sg.step), sg.layer, b, h, smem);
+      task_select(P, select_io(a, sg.layer, sg.slot, sg.step), sg.layer, b, h, smem,
+                  st == ST_SELA ? SEL_A : st == ST_SELECT ? SEL_B : SEL_AB);
       break;
     }
-    case ST_SELA: {
-      const int b = blk / P.H, h = blk % P.H;
-      task_select_a(P, select_io(a, sg.layer, sg.slot, sg.step), b, h, smem);
+    case ST_CNTB: {
+      const int parts = (P.words + kBitWords - 1) / kBitWords;
+      task_counts_from_bits(P, a.bits, reinterpret_cast<uint8_t*>(a.ws + a.w.counts), sg.layer, blk / parts,
+                            blk % parts);
+      if (a.p_raw) {
+        // scores from the caller: no score pass has cleared the histograms
+        uint32_t* hist = reinterpret_cast<uint32_t*>(a.ws + (size_t)sg.slot * a.w.slot_bytes + a.w.hist);
+        const int64_t n = (int64_t)P.batch * 2 * P.H * kHistBins;
+        for (int64_t i = (int64_t)blk * kThreads + threadIdx.x; i < n; i += (int64_t)sg.count * kThreads) hist[i] = 0u;
+      }
       break;
     }
     case ST_COUNT: {
