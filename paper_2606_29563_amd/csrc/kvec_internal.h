@@ -12,6 +12,7 @@ namespace kvec {
 constexpr int kThreads = 512;  // every work-group of the step kernel: 8 waves
 constexpr int kPipeDepth = 11;         // launches between a layer's first and last stage
 constexpr int kPipeDepthLse = 7;       // the same when the row normalisers are given
+constexpr int kPipeDepthWide = 7;      // ... when all rows are scored at once (5 when given)
 constexpr int kRing = kPipeDepth + 1;  // layers in flight in the software pipeline
 
 constexpr int kTileMax = 512;     // keys per score work-group at long prefixes

@@ -32,6 +32,10 @@
 // their pool at j-3, prep at j-4, select A at j-5, select B and count at
 // j-6, gather at j-7.
 //
+// Small problems run the wide pipeline: pass 1, lse, pass 2 and pool of every
+// row and head at j .. j-3, prep at j-4, select A at j-5, select B and count
+// at j-6, gather at j-7 (two less with given normalisers).
+//
 // Work-group IDs are dispatched round-robin over the 8 XCDs, each with its
 // own L2.  Within a stage, consecutive tasks (e.g. the row tiles of one key
 // tile, which read the same K rows) are mapped to work-groups on the same
@@ -208,6 +212,21 @@ hipError_t score_stages(StepArgs a, const Workspace& w, hipStream_t s, int count
   return hipSuccess;
 }
 
+// Whether a model step scores all window rows of every head in one pass per
+// layer (the wide pipeline: four stages and launches shorter, two with given
+// normalisers) instead of the extended rows of the H_top heads four launches
+// later.  It scores more rows (all heads'), which costs nothing while a
+// launch's score work-groups leave compute units idle, so the line is at three
+// quarters of the 256 (the short stages take the rest).  Measured, us per step
+// split / wide: 128 work-groups (2k, 32 layers) 621 / 572, Qwen heads 16k
+// 1486 / 1377, given normalisers 4k 654 / 641 and 16k 1223 / 1172; 192 (12k,
+// given) 860 / 822; 16 (1k, float32, two layers) 262 / 158; but 256 (4k)
+// 635 / 968 and 256 (8k, 64 rows, given) 843 / 1425.
+bool wide_pays(const Problem& P, bool lse) {
+  const int64_t tiles = lse ? P.n_kt2 : P.n_kt1 + P.n_kt2;
+  return P.batch * tiles * P.n_rtg <= 192;
+}
+
 hipError_t set_lds_limit(const Problem& P, const Workspace& w) {
   static_assert(kThreads == 512, "task code assumes 512-thread work-groups");
   if (w.lds_bytes <= 65536) return hipSuccess;
@@ -230,6 +249,26 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
   // several steps: one pipeline over their n_steps x L layers in order (a
   // layer's selection chain only links layers of its own step)
   const int ns = m.n_steps > 0 ? m.n_steps : 1;
+  // (a caller's events mark the launches of the split pipeline, and its score
+  // outputs hold the extended rows' scores of the H_top heads only)
+  if (!ev && !m.sc_p && wide_pays(P, m.lse != nullptr)) {
+    const int d = m.lse ? 2 : 0;  // stages that the given normalisers save
+    for (int j = 0; j < ns * P.L + kPipeDepthWide - d; ++j) {
+      if (!m.lse) {
+        set_seg(a, ST_PASS1, j, ns);
+        set_seg(a, ST_LSE, j - 1, ns);
+      }
+      set_seg(a, ST_PASS2, j - 2 + d, ns);
+      set_seg(a, ST_POOL, j - 3 + d, ns);
+      set_seg(a, ST_PREP, j - 4 + d, ns);
+      set_seg(a, ST_SELA, j - 5 + d, ns);
+      set_seg(a, ST_SELECT, j - 6 + d, ns);
+      set_seg(a, ST_COUNT, j - 6 + d, ns);
+      set_seg(a, ST_GATHER, j - 7 + d, ns);
+      if ((e = launch(a, w, s)) != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
   if (m.lse) {
     // The row normalisers come from the caller (the log-sum-exp of the
     // layer's prefill attention): no pass 1, a shorter pipeline.

@@ -1,0 +1,111 @@
+"""The routes a model step can take give the same bytes: the wide pipeline
+(small problems), the split pipeline (the same call with profiling events), and
+the per-layer entry points, which run the selection as one task.  Equality is
+exact: every route adds the same terms in the same order."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _config(kv, T, H, G, d, dtype, batch=1, O=32, B=None, layers=4, beta=0.25):
+    return kv.Config(batch=batch, n_layers=layers, n_kv_heads=H, n_q_heads=H * G, head_dim=d, seq_len=T,
+                     window=O, window_ext=2 * O, budget=B or O + T // 8, pool_kernel=7,
+                     n_adjust_heads=min(3, H), lam=1.0, beta=beta, dtype=dtype)
+
+
+class Step:
+    def __init__(self, kv, cfg, dtype, seed, zero_q=False):
+        import torch
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        L, b, H, T, d, B = cfg.n_layers, cfg.batch, cfg.n_kv_heads, cfg.seq_len, cfg.head_dim, cfg.budget
+        self.kv, self.cfg, W = kv, cfg, min(cfg.window_ext, T)
+        self.q = torch.randn((L, b, cfg.n_q_heads, W, d), generator=g, device="cuda").to(dtype)
+        if zero_q:
+            self.q.zero_()
+        self.k = torch.randn((L, b, H, T, d), generator=g, device="cuda").to(dtype)
+        self.v = torch.randn((L, b, H, T, d), generator=g, device="cuda").to(dtype)
+        x = torch.matmul(self.q.float().reshape(L, b, H, -1, d), self.k.float().transpose(-1, -2).contiguous())
+        x = x.reshape(L, b, cfg.n_q_heads, W, T) / d ** 0.5
+        hidden = torch.arange(T, device="cuda")[None] > torch.arange(T - W, T, device="cuda")[:, None]
+        self.lse = x.masked_fill_(hidden, -float("inf")).logsumexp(-1)
+        self.ws = torch.empty(kv.kvec_workspace_size(cfg), dtype=torch.uint8, device="cuda")
+
+    def outputs(self):
+        import torch
+        c = self.cfg
+        shape = (c.n_layers, c.batch, c.n_kv_heads, c.budget)
+        return (torch.zeros((c.batch, c.n_layers, (c.seq_len + 63) // 64), dtype=torch.int64, device="cuda"),
+                torch.full(shape, -7, dtype=torch.int32, device="cuda"),
+                torch.zeros(shape + (c.head_dim,), dtype=self.k.dtype, device="cuda"),
+                torch.zeros(shape + (c.head_dim,), dtype=self.k.dtype, device="cuda"))
+
+    def model(self, given, split):
+        import torch
+        o = self.outputs()
+        ev = None
+        if split:
+            n = (self.kv.kvec_profile_points_lse if given else self.kv.kvec_profile_points)(self.cfg)
+            keep = [torch.cuda.Event() for _ in range(n)]
+            for e in keep:
+                e.record()
+            ev = [e.cuda_event for e in keep]
+        if given:
+            self.kv.kvec_evict_model_lse(self.cfg, self.q, self.lse, self.k, self.v, *o, self.ws, events=ev)
+        else:
+            self.kv.kvec_evict_model(self.cfg, self.q, self.k, self.v, *o, self.ws, events=ev)
+        torch.cuda.synchronize()
+        return o
+
+    def layers(self, given):
+        import torch
+        bits, idx, ko, vo = o = self.outputs()
+        for l in range(self.cfg.n_layers):
+            if given:
+                self.kv.kvec_evict_layer_lse(self.cfg, l, self.q[l], self.lse[l], self.k[l], self.v[l], bits, idx[l],
+                                             ko[l], vo[l], self.ws)
+            else:
+                self.kv.kvec_evict_layer(self.cfg, l, self.q[l], self.k[l], self.v[l], bits, idx[l], ko[l], vo[l],
+                                         self.ws)
+        torch.cuda.synchronize()
+        return o
+
+
+# (T, H, G, d, dtype, batch, O): both sides of the line of 192 score work-groups
+# (wide below it), ragged lengths, one and two row tiles per work-group, row
+# tiles that mix last-O and earlier rows
+CASES = [
+    (1024, 4, 2, 64, "f32", 1, 32),
+    (777, 8, 4, 128, "bf16", 2, 32),
+    (3071, 8, 4, 128, "bf16", 1, 32),
+    (3073, 8, 4, 128, "bf16", 1, 32),
+    (4096, 4, 7, 128, "bf16", 1, 32),
+    (2000, 8, 4, 128, "bf16", 1, 20),
+    (65, 2, 2, 64, "bf16", 3, 16),
+]
+
+
+@pytest.mark.parametrize("given", [False, True], ids=["two-pass", "given"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"T{c[0]}-H{c[1]}-G{c[2]}-{c[4]}-b{c[5]}-O{c[6]}")
+def test_routes_agree(gpu_lib, case, given):
+    import torch
+    T, H, G, d, dt, batch, O = case
+    f32 = dt == "f32"
+    cfg = _config(gpu_lib, T, H, G, d, gpu_lib.KVEC_F32 if f32 else gpu_lib.KVEC_BF16, batch, O)
+    s = Step(gpu_lib, cfg, torch.float32 if f32 else torch.bfloat16, T)
+    want = s.model(given, split=True)
+    for got in (s.model(given, split=False), s.layers(given)):
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T", [11500, 13000], ids=["members-in-lds", "members-spilled"])
+def test_routes_agree_all_members(gpu_lib, T):
+    """Zero queries: all scores tie, so every token is a member; the longer
+    prompt has more than a selection task holds in LDS (about 11.7 thousand)."""
+    import torch
+    cfg = _config(gpu_lib, T, 2, 2, 64, gpu_lib.KVEC_BF16, layers=3)
+    s = Step(gpu_lib, cfg, torch.bfloat16, 5, zero_q=True)
+    want = s.model(False, split=True)
+    for got in (s.model(False, split=False), s.layers(False)):
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
