@@ -17,8 +17,9 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 # (dtype, head_dim) pair, in parallel translation units
 SOURCES = [("kvec_api.hip", "kvec_api", []), ("kvec_pipeline.hip", "kvec_pipeline", []),
            ("kvec_decode.hip", "kvec_decode", [])] + [
-    ("kvec_step_inst.hip", f"kvec_step_{tt.lower()}_d{d}", [f"-DKVEC_INST_TT={tt}", f"-DKVEC_INST_D={d}"])
-    for tt in ("BF16", "F32") for d in (64, 128)]
+    ("kvec_step_inst.hip", f"kvec_step_{tt.lower()}_d{d}{'_long' if long == 'true' else ''}",
+     [f"-DKVEC_INST_TT={tt}", f"-DKVEC_INST_D={d}", f"-DKVEC_INST_LONG={long}"])
+    for tt, long in (("BF16", "false"), ("F32", "false"), ("BF16", "true")) for d in (64, 128)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

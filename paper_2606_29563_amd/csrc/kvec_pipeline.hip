@@ -135,8 +135,9 @@ int seg_count(const Problem& P, int st) {
 }
 
 StepFn pick(const Problem& P) {
-  if (P.esize == 2) return P.D == 64 ? pick_g<BF16, 64>(P.G) : pick_g<BF16, 128>(P.G);
-  return P.D == 64 ? pick_g<F32, 64>(P.G) : pick_g<F32, 128>(P.G);
+  if (P.sub2 > 1) return P.D == 64 ? pick_g<BF16, 64, true>(P.G) : pick_g<BF16, 128, true>(P.G);
+  if (P.esize == 2) return P.D == 64 ? pick_g<BF16, 64, false>(P.G) : pick_g<BF16, 128, false>(P.G);
+  return P.D == 64 ? pick_g<F32, 64, false>(P.G) : pick_g<F32, 128, false>(P.G);
 }
 
 StepArgs base_args(const Geometry& g, char* ws, const Workspace& w) {
@@ -227,6 +228,27 @@ bool wide_pays(const Problem& P, bool lse) {
   return P.batch * tiles * P.n_rtg <= 192;
 }
 
+// Keys per score work-group of a model step.  About 10 of the 30-odd us that a
+// work-group takes for 512 keys are fixed (code and first keys from memory,
+// queries, normalisers, write-out), so where a launch has many rounds of
+// work-groups, each takes two or four tiles in a row: pass 1 as one longer
+// tile, pass 2 staging and writing out one tile after the other.  With few
+// rounds the coarser last round costs more than that saves.  Measured against
+// one tile each, by the score work-groups of a launch: up to 650 0.95 to 1.14
+// (mostly worse), 704 0.93 to 1.02, 860 to 1060 0.97, 1300 to 1410 0.89 to
+// 0.93, 2150 0.93 (four tiles 0.94), 2600 0.93 (four 0.91), 2800 0.90 (four
+// 0.88).
+void lengthen_tiles(Problem& P, bool lse) {
+  if (P.esize != 2 || P.tile1 != kTileMax || P.tile2 != kTileMax) return;
+  const int64_t passes = lse ? 1 : 2;
+  const int64_t n = passes * ((int64_t)P.batch * P.n_kt1 * P.n_rtg_base + ext_wgs(P, P.n_kt1));
+  const int sub = n >= 10 * 256 ? 4 : n >= 11 * 64 ? 2 : 1;
+  P.tile1 *= sub;
+  P.n_kt1 = (P.T + P.tile1 - 1) / P.tile1;
+  P.sub2 = sub;
+  P.n_kt2 = (P.Tc + P.tile2 * sub - 1) / (P.tile2 * sub);
+}
+
 hipError_t set_lds_limit(const Problem& P, const Workspace& w) {
   static_assert(kThreads == 512, "task code assumes 512-thread work-groups");
   if (w.lds_bytes <= 65536) return hipSuccess;
@@ -269,6 +291,8 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
     }
     return hipSuccess;
   }
+  lengthen_tiles(a.P, m.lse != nullptr);
+  if ((e = set_lds_limit(a.P, w)) != hipSuccess) return e;
   if (m.lse) {
     // The row normalisers come from the caller (the log-sum-exp of the
     // layer's prefill attention): no pass 1, a shorter pipeline.

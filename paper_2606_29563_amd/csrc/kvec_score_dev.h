@@ -294,7 +294,11 @@ struct KeyRing {
 // so low bits could be lost) is flagged with an infinite sum and the row
 // normaliser recomputes that (row, tile) partial exactly.
 
-template <class TT, int D, int G, int PASS>
+// LONG: a pass-2 work-group takes P.sub2 staged tiles in a row (model steps of
+// many work-groups).  A variant of its own, in kernels of its own: the offsets
+// within the staged tile and the write-out inside the key loop cost every
+// other launch about 3%.
+template <class TT, int D, int G, int PASS, bool LONG>
 struct ScoreTile {
   using Tl = Tiling<G>;
   static constexpr int RB = Tl::RB, NB = Tl::NB, WR = Tl::WR;
@@ -305,7 +309,7 @@ struct ScoreTile {
   const ScoreIO& io;
   int b, kt, rtg;
   int lane, c, n, tpw, h, hs, nh, slot, rt;
-  bool active, idle, exch;
+  bool active, idle, exch, ext_part;
   int r_lo, base_lo, tend, ks, ke, lim_min, nsteps, rr0;
   const char* kbase;
   bool tile_base, tile_mixed, wg_base;
@@ -342,6 +346,7 @@ struct ScoreTile {
     c = lane >> 4;
     n = lane & 15;
     const bool ext = part == PART_EXT;
+    ext_part = ext;
     nh = ext ? 1 : P.H;
     tpw = 8 / nh;
     hs = w % nh;
@@ -361,7 +366,7 @@ struct ScoreTile {
       for (int i = 0; i < 4; ++i) pos[rb][i] = P.T - P.Wn + (r_lo + rb * 16 + 4 * c + i);
 
     tend = PASS == 1 ? P.T : P.Tc;
-    const int tile = PASS == 1 ? P.tile1 : P.tile2;
+    const int tile = PASS == 1 ? P.tile1 : LONG ? P.tile2 * P.sub2 : P.tile2;
     ks = kt * tile;
     ke = min(ks + tile, tend);
     lim_min = P.T - P.Wn + max(r_lo, 0);
@@ -497,6 +502,9 @@ struct ScoreTile {
       }
   }
 
+  // Offset of step s in the staged tile.
+  __device__ __forceinline__ int staged(int s) const { return LONG ? (s * 16 & (P.tile2 - 1)) : s * 16; }
+
   template <bool MASKED, int EP>
   __device__ __forceinline__ void epilogue(int s) {
     const int t = ks + 16 * s + n;
@@ -532,10 +540,10 @@ struct ScoreTile {
         for (int i = rb == 0 ? 1 : 0; i < 4; ++i) s_all += gs[rb][i];
       if constexpr (EP != EP_GEN) {
         s_all = col_sum4(s_all);
-        if (c == 0) obuf[hs * P.tile2 + s * 16 + n] = s_all;
+        if (c == 0) obuf[hs * P.tile2 + staged(s) + n] = s_all;
         if constexpr (EP == EP_IMP) {
           if (nh == 1) {
-            if (c == 0) ibuf[s * 16 + n] = s_all;
+            if (c == 0) ibuf[staged(s) + n] = s_all;
           } else {
             fold_max<false>(s, gs);
           }
@@ -558,13 +566,13 @@ struct ScoreTile {
       if (c == 0) {
         // with one sum per head (no mixed tiles) the last-O sum of a base
         // tile equals its all-row sum and is never read for other tiles
-        obuf[(hs * P.nsum) * P.tile2 + s * 16 + n] = s_all;
-        if (P.nsum == 2) obuf[(hs * 2 + 1) * P.tile2 + s * 16 + n] = s_base;
+        obuf[(hs * P.nsum) * P.tile2 + staged(s) + n] = s_all;
+        if (P.nsum == 2) obuf[(hs * 2 + 1) * P.tile2 + staged(s) + n] = s_base;
       }
       if (tile_base) {
         if (nh == 1) {
           // one head: the max over heads is the head itself
-          if (c == 0) ibuf[s * 16 + n] = s_base;
+          if (c == 0) ibuf[staged(s) + n] = s_base;
         } else {
           fold_max<true>(s, gs);
         }
@@ -597,7 +605,7 @@ struct ScoreTile {
         }
       }
       v = col_sum4(v);
-      if (ok && rg == 0) ibuf[period * P.SK + kc] = v;
+      if (ok && rg == 0) ibuf[(LONG ? ((period * P.SK) & (P.tile2 - 1)) : period * P.SK) + kc] = v;
     }
   }
 
@@ -629,6 +637,8 @@ struct ScoreTile {
     }
     if constexpr (PASS == 2) {
       if (exch && (((s + 1) * 16) & (P.SK - 1)) == 0) exchange(s);
+      // every staged tile but the last is written out here
+      if (LONG && F == 1 && (((s + 1) * 16) & (P.tile2 - 1)) == 0 && s + 1 < nsteps) write_out(s / (P.tile2 / 16));
     }
     if constexpr (NB >= 7) {
       // The next step's products read this fragment only after this step's
@@ -681,7 +691,7 @@ struct ScoreTile {
   __device__ __forceinline__ void execute() {
     if (idle) {
       // no tile: only meet the work-group barrier of the write-out
-      if constexpr (PASS == 2) lds_barrier();
+      if constexpr (PASS == 2 && !LONG) lds_barrier();
       return;
     }
     // Steps 0..kAhead-1 are in flight before the loop, the queries loaded
@@ -771,25 +781,35 @@ struct ScoreTile {
       io.lse_part[(((int64_t)b * P.HQ + j) * P.Wn + r) * P.n_kt1 + kt] = make_float2(m, l);
   }
 
-  __device__ __forceinline__ void finish() {
-    if constexpr (PASS == 2) {
-      lds_barrier();
-      if (active) {
-        const int64_t o = (((int64_t)b * P.n_rt + rt) * P.H + h) * P.Tc;
-        for (int i = lane; i < P.tile2; i += 64) {
-          const int t = ks + i;
-          if (t < P.Tc) {
-            io.psum_all[o + t] = obuf[(hs * P.nsum) * P.tile2 + i];
-            if (P.nsum == 2) io.psum_base[o + t] = obuf[(hs * 2 + 1) * P.tile2 + i];
-          }
-        }
-        if (tile_base && hs == 0) {
-          for (int i = lane; i < P.tile2; i += 64) {
-            const int t = ks + i;
-            if (t < P.Tc) io.ipart[((int64_t)b * P.n_rt + rt) * P.Tc + t] = ibuf[i];
-          }
+  // Pass 2: the staged sums of staged tile `sub` of this work-group's keys.
+  // The barrier orders the importance (summed by all waves of the slot) before
+  // its write-out, and an exchange's clearing before the next tile's first
+  // fold.  EXT waves share nothing; with LONG they may hold different numbers
+  // of tiles and meet no barrier.
+  __device__ __forceinline__ void write_out(int sub) {
+    if (!LONG || !ext_part) lds_barrier();
+    if (active) {
+      const int k0 = LONG ? ks + sub * P.tile2 : ks;
+      const int64_t o = (((int64_t)b * P.n_rt + rt) * P.H + h) * P.Tc;
+      for (int i = lane; i < P.tile2; i += 64) {
+        const int t = k0 + i;
+        if (t < P.Tc) {
+          io.psum_all[o + t] = obuf[(hs * P.nsum) * P.tile2 + i];
+          if (P.nsum == 2) io.psum_base[o + t] = obuf[(hs * 2 + 1) * P.tile2 + i];
         }
       }
+      if (tile_base && hs == 0) {
+        for (int i = lane; i < P.tile2; i += 64) {
+          const int t = k0 + i;
+          if (t < P.Tc) io.ipart[((int64_t)b * P.n_rt + rt) * P.Tc + t] = ibuf[i];
+        }
+      }
+    }
+  }
+
+  __device__ __forceinline__ void finish() {
+    if constexpr (PASS == 2) {
+      write_out(LONG ? (nsteps - 1) / (P.tile2 / 16) : 0);
     } else {
       // Row sums of 4 blocks (16 quantities: block, row of the lane group) at a
       // time; lane n of each row ends with quantity n and stores its partial.
@@ -800,10 +820,10 @@ struct ScoreTile {
   }
 };
 
-template <class TT, int D, int G, int PASS>
+template <class TT, int D, int G, int PASS, bool LONG>
 __device__ __forceinline__ void score_tile(const Problem& P, const ScoreIO& io, int b, int kt, int rtg,
                                            float* smem, Part part = PART_ALL, uint32_t hmask = 0) {
-  ScoreTile<TT, D, G, PASS> st(P, io, b, kt, rtg, smem, part, hmask);
+  ScoreTile<TT, D, G, PASS, LONG> st(P, io, b, kt, rtg, smem, part, hmask);
   st.execute();
 }
 

@@ -215,7 +215,8 @@ __device__ __forceinline__ int ext_task(const Problem& P, const StepArgs& a, con
   return b;
 }
 
-template <class TT, int D, int G>
+// LONG: the model steps whose pass-2 work-groups take several tiles (bf16).
+template <class TT, int D, int G, bool LONG = false>
 __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
   extern __shared__ __align__(16) char smem[];
   const Problem P = a.P;
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       const int n_rtg = part == PART_BASE ? P.n_rtg_base : P.n_rtg;
       const int per_b = P.n_kt1 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
-      score_tile<TT, D, G, 1>(P, score_io(a, sg.layer, sg.slot, sg.step), b, rem / n_rtg, rem % n_rtg,
+      score_tile<TT, D, G, 1, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, rem / n_rtg, rem % n_rtg,
                               reinterpret_cast<float*>(smem), part, 0u);
       break;
     }
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       int kt, rte;
       uint32_t hm;
       const int b = ext_task(P, a, sg, P.n_kt1, blk, kt, rte, hm);
-      score_tile<TT, D, G, 1>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
+      score_tile<TT, D, G, 1, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
                               reinterpret_cast<float*>(smem), PART_EXT, hm);
       break;
     }
@@ -306,7 +307,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       int kt, rte;
       uint32_t hm;
       const int b = ext_task(P, a, sg, P.n_kt2, blk, kt, rte, hm);
-      score_tile<TT, D, G, 2>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
+      score_tile<TT, D, G, 2, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
                               reinterpret_cast<float*>(smem), PART_EXT, hm);
       break;
     }
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       const int per_b = P.n_kt2 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
       const ScoreIO io = score_io(a, sg.layer, sg.slot, sg.step);
-      score_tile<TT, D, G, 2>(P, io, b, rem / n_rtg, rem % n_rtg, reinterpret_cast<float*>(smem),
+      score_tile<TT, D, G, 2, LONG>(P, io, b, rem / n_rtg, rem % n_rtg, reinterpret_cast<float*>(smem),
                               part, 0u);
       {
         // Clear this sequence's histograms for the pool stages of this layer.
@@ -368,13 +369,16 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
 
 typedef void (*StepFn)(StepArgs);
 
-// The step kernel of one (dtype, head_dim) for group size G (1..8).
-template <class TT, int D>
+// The step kernel of one (dtype, head_dim) for group size G (1..8), and
+// its LONG variant.
+template <class TT, int D, bool LONG>
 StepFn pick_g(int G);
-template <> StepFn pick_g<BF16, 64>(int G);
-template <> StepFn pick_g<BF16, 128>(int G);
-template <> StepFn pick_g<F32, 64>(int G);
-template <> StepFn pick_g<F32, 128>(int G);
+template <> StepFn pick_g<BF16, 64, false>(int G);
+template <> StepFn pick_g<BF16, 128, false>(int G);
+template <> StepFn pick_g<BF16, 64, true>(int G);
+template <> StepFn pick_g<BF16, 128, true>(int G);
+template <> StepFn pick_g<F32, 64, false>(int G);
+template <> StepFn pick_g<F32, 128, false>(int G);
 
 }  // namespace step
 }  // namespace kvec

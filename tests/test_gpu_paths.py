@@ -109,3 +109,35 @@ def test_routes_agree_all_members(gpu_lib, T):
     for got in (s.model(False, split=False), s.layers(False)):
         for a, b in zip(got, want):
             assert torch.equal(a, b)
+
+
+# batches whose launches hold enough score work-groups for two (704) and four
+# (2560) key tiles each; a ragged last tile, and row tiles of one and of two
+# 16-row blocks
+LONG = [(16384 + 77, 1, 4, 12), (16384 + 77, 2, 1, 24), (20011, 1, 4, 44)]
+
+
+@pytest.mark.parametrize("case", LONG, ids=lambda c: f"T{c[0]}-H{c[1]}-G{c[2]}-b{c[3]}")
+def test_long_score_work_groups(gpu_lib, case):
+    import torch
+    kv = gpu_lib
+    T, H, G, batch = case
+    cfg = _config(kv, T, H, G, 64, kv.KVEC_BF16, batch, layers=1, B=512)
+    s = Step(kv, cfg, torch.bfloat16, 11)
+    # given normalisers: the same bytes as the per-layer call (one tile each)
+    for a, b in zip(s.model(True, split=False), s.layers(True)):
+        assert torch.equal(a, b)
+    # two passes: scores of the step against those of kvec_score.  The
+    # normalisers add up to 2048 / 16 terms a lane in another order: at most
+    # 128 float32 roundings (8e-6) apart
+    Tc = T - cfg.window
+    p, pe = (torch.zeros((1, batch, H, Tc), device="cuda") for _ in range(2))
+    imp = torch.zeros((1, batch, Tc), device="cuda")
+    htop = torch.zeros((1, batch), dtype=torch.int32, device="cuda")
+    kv.kvec_evict_model_scores(cfg, s.q, s.k, s.v, *s.outputs(), p, pe, imp, htop, s.ws)
+    p1, pe1, imp1 = torch.empty_like(p[0]), torch.empty_like(p[0]), torch.empty_like(imp[0])
+    kv.kvec_score(cfg, s.q[0], s.k[0], p1, pe1, imp1, s.ws)
+    torch.cuda.synchronize()
+    assert torch.allclose(p[0], p1, rtol=8e-6, atol=0)
+    assert torch.allclose(pe[0], pe1, rtol=8e-6, atol=0)  # every head is in H_top (H <= 3)
+    assert torch.allclose(imp[0], imp1, rtol=8e-6, atol=0)
