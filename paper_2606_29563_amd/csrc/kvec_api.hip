@@ -102,8 +102,10 @@ kvec_status make_geometry(const kvec_config* c, Geometry* g) {
         break;
       }
   if (!x.tile2) return KVEC_ERR_UNSUPPORTED;
-  x.sub2 = 1;  // a model step may raise it and tile1 (lengthen_tiles)
+  x.sub = 1;  // a model step may raise it (lengthen_tiles)
   x.n_kt2 = (x.Tc + x.tile2 - 1) / x.tile2;
+  x.n_wt1 = x.n_kt1;
+  x.n_wt2 = x.n_kt2;
   x.n_pool = (x.Tc + kPoolChunk - 1) / kPoolChunk;
   x.n_prep = (x.Tc + kPrepChunk - 1) / kPrepChunk;
   x.words = (x.T + 63) / 64;

@@ -67,7 +67,8 @@ struct Problem {
   int batch, L, H, HQ, G, D, T, O, Wn, Tc, B, M, Kp, pool, delta_eff;
   float lam, sc, inv_go, inv_gwn;
   int WR, n_rt, n_rt_base, n_rtg, n_kt1, n_kt2, SK, tile1, tile2;
-  int sub2;        // staged tiles of tile2 keys per pass-2 work-group
+  int sub;         // key tiles per score work-group
+  int n_wt1, n_wt2;  // score work-groups' key ranges (sub tiles each) per row tile
   int sk_shift;    // log2(SK): exchange periods are powers of two
   int nsum;        // pass-2 per-key sums per head: 1 when O is a multiple of WR (no row
                    // tile holds both last-O and earlier rows), else 2

@@ -116,15 +116,15 @@ int seg_count(const Problem& P, int st) {
     case ST_SELAB: return P.batch * P.H;
     case ST_COUNT: return P.batch * ((P.words + kCountWords - 1) / kCountWords);
     case ST_CNTB: return P.batch * ((P.words + kBitWords - 1) / kBitWords);
-    case ST_PASS1: return P.batch * P.n_kt1 * P.n_rtg;
-    case ST_P1B: return P.batch * P.n_kt1 * P.n_rtg_base;
-    case ST_P1X: return ext_wgs(P, P.n_kt1);
+    case ST_PASS1: return P.batch * P.n_wt1 * P.n_rtg;
+    case ST_P1B: return P.batch * P.n_wt1 * P.n_rtg_base;
+    case ST_P1X: return ext_wgs(P, P.n_wt1);
     case ST_LSE:
     case ST_LSEB: return P.batch * lse_tasks_per_seq(P, st);
     case ST_LSEX: return P.n_rt_x ? P.batch * lse_tasks_per_seq(P, st) : 0;
-    case ST_PASS2: return P.batch * P.n_kt2 * P.n_rtg;
-    case ST_P2B: return P.batch * P.n_kt2 * P.n_rtg_base;
-    case ST_P2X: return ext_wgs(P, P.n_kt2);
+    case ST_PASS2: return P.batch * P.n_wt2 * P.n_rtg;
+    case ST_P2B: return P.batch * P.n_wt2 * P.n_rtg_base;
+    case ST_P2X: return ext_wgs(P, P.n_wt2);
     case ST_POOL:
     case ST_POOLB: return P.batch * P.H * ((P.n_pool + kPoolPer - 1) / kPoolPer);
     case ST_POOLX: return ext ? P.batch * P.delta_eff * ((P.n_pool + kPoolPer - 1) / kPoolPer) : 0;
@@ -135,7 +135,7 @@ int seg_count(const Problem& P, int st) {
 }
 
 StepFn pick(const Problem& P) {
-  if (P.sub2 > 1) return P.D == 64 ? pick_g<BF16, 64, true>(P.G) : pick_g<BF16, 128, true>(P.G);
+  if (P.sub > 1) return P.D == 64 ? pick_g<BF16, 64, true>(P.G) : pick_g<BF16, 128, true>(P.G);
   if (P.esize == 2) return P.D == 64 ? pick_g<BF16, 64, false>(P.G) : pick_g<BF16, 128, false>(P.G);
   return P.D == 64 ? pick_g<F32, 64, false>(P.G) : pick_g<F32, 128, false>(P.G);
 }
@@ -231,8 +231,7 @@ bool wide_pays(const Problem& P, bool lse) {
 // Keys per score work-group of a model step.  About 10 of the 30-odd us that a
 // work-group takes for 512 keys are fixed (code and first keys from memory,
 // queries, normalisers, write-out), so where a launch has many rounds of
-// work-groups, each takes two or four tiles in a row: pass 1 as one longer
-// tile, pass 2 staging and writing out one tile after the other.  With few
+// work-groups, each takes two or four tiles in a row.  With few
 // rounds the coarser last round costs more than that saves.  Measured against
 // one tile each, by the score work-groups of a launch: up to 650 0.95 to 1.14
 // (mostly worse), 704 0.93 to 1.02, 860 to 1060 0.97, 1300 to 1410 0.89 to
@@ -243,10 +242,9 @@ void lengthen_tiles(Problem& P, bool lse) {
   const int64_t passes = lse ? 1 : 2;
   const int64_t n = passes * ((int64_t)P.batch * P.n_kt1 * P.n_rtg_base + ext_wgs(P, P.n_kt1));
   const int sub = n >= 10 * 256 ? 4 : n >= 11 * 64 ? 2 : 1;
-  P.tile1 *= sub;
-  P.n_kt1 = (P.T + P.tile1 - 1) / P.tile1;
-  P.sub2 = sub;
-  P.n_kt2 = (P.Tc + P.tile2 * sub - 1) / (P.tile2 * sub);
+  P.sub = sub;
+  P.n_wt1 = (P.n_kt1 + sub - 1) / sub;
+  P.n_wt2 = (P.n_kt2 + sub - 1) / sub;
 }
 
 hipError_t set_lds_limit(const Problem& P, const Workspace& w) {

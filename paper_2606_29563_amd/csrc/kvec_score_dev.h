@@ -294,8 +294,10 @@ struct KeyRing {
 // so low bits could be lost) is flagged with an infinite sum and the row
 // normaliser recomputes that (row, tile) partial exactly.
 
-// LONG: a pass-2 work-group takes P.sub2 staged tiles in a row (model steps of
-// many work-groups).  A variant of its own, in kernels of its own: the offsets
+// LONG: a work-group takes P.sub key tiles in a row (model steps of many
+// work-groups): pass 1 stores the partials of one tile after the other, so the
+// sums are as short as with one tile each (the block references stay the first
+// tile's), pass 2 stages and writes out one tile after the other.  A variant of its own, in kernels of its own: the offsets
 // within the staged tile and the write-out inside the key loop cost every
 // other launch about 3%.
 template <class TT, int D, int G, int PASS, bool LONG>
@@ -366,7 +368,7 @@ struct ScoreTile {
       for (int i = 0; i < 4; ++i) pos[rb][i] = P.T - P.Wn + (r_lo + rb * 16 + 4 * c + i);
 
     tend = PASS == 1 ? P.T : P.Tc;
-    const int tile = PASS == 1 ? P.tile1 : LONG ? P.tile2 * P.sub2 : P.tile2;
+    const int tile = (PASS == 1 ? P.tile1 : P.tile2) * (LONG ? P.sub : 1);
     ks = kt * tile;
     ke = min(ks + tile, tend);
     lim_min = P.T - P.Wn + max(r_lo, 0);
@@ -640,6 +642,16 @@ struct ScoreTile {
       // every staged tile but the last is written out here
       if (LONG && F == 1 && (((s + 1) * 16) & (P.tile2 - 1)) == 0 && s + 1 < nsteps) write_out(s / (P.tile2 / 16));
     }
+    if constexpr (PASS == 1 && LONG) {
+      // the partials of every tile but the last are stored here
+      if (F == 1 && (((s + 1) * 16) & (P.tile1 - 1)) == 0 && s + 1 < nsteps) {
+        store_tile(s / (P.tile1 / 16));
+#pragma unroll
+        for (int bk = 0; bk < NB; ++bk)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) lsum[bk][i] = 0.f;
+      }
+    }
     if constexpr (NB >= 7) {
       // The next step's products read this fragment only after this step's
       // exponentials: with seven or eight blocks two sets of products would
@@ -760,7 +772,7 @@ struct ScoreTile {
   // tile, one store for the wave (compile-time indices only, so the sums stay
   // in registers).
   template <int Q0>
-  __device__ __forceinline__ void store_partials() {
+  __device__ __forceinline__ void store_partials(int sub) {
     float l = row_transpose_sum16(
         n, lsum[Q0][0], lsum[Q0][1], lsum[Q0][2], lsum[Q0][3], lsum[Q0 + 1][0], lsum[Q0 + 1][1],
         lsum[Q0 + 1][2], lsum[Q0 + 1][3], lsum[Q0 + 2][0], lsum[Q0 + 2][1], lsum[Q0 + 2][2],
@@ -773,12 +785,12 @@ struct ScoreTile {
     const float m0 = mref[Q0], m1 = mref[Q0 + 1], m2 = mref[Q0 + 2], m3 = mref[Q0 + 3];
     const float mb = bq == 0 ? m0 : bq == 1 ? m1 : bq == 2 ? m2 : m3;
     // rows past the tile's first key hold no valid key here: (-inf, 0)
-    const bool has_keys = ks <= P.T - P.Wn + r;
+    const bool has_keys = ks + sub * P.tile1 <= P.T - P.Wn + r;
     const float m = has_keys ? mb : -INFINITY;
     if (!has_keys) l = 0.f;
     else if (!(l >= 0x1p-64f && l < INFINITY)) l = INFINITY;  // exact recompute
     if (active && r >= 0 && bk < NB)
-      io.lse_part[(((int64_t)b * P.HQ + j) * P.Wn + r) * P.n_kt1 + kt] = make_float2(m, l);
+      io.lse_part[(((int64_t)b * P.HQ + j) * P.Wn + r) * P.n_kt1 + (LONG ? kt * P.sub + sub : kt)] = make_float2(m, l);
   }
 
   // Pass 2: the staged sums of staged tile `sub` of this work-group's keys.
@@ -807,15 +819,20 @@ struct ScoreTile {
     }
   }
 
+  // Pass 1: the partials of tile `sub` of this work-group.  Row sums of 4 blocks
+  // (16 quantities: block, row of the lane group) at a time; lane n of each
+  // row ends with quantity n and stores its partial.
+  __device__ __forceinline__ void store_tile(int sub) {
+    static_assert(NBP == 4 || NBP == 8, "blocks in groups of four");
+    store_partials<0>(sub);
+    if constexpr (NBP == 8) store_partials<4>(sub);
+  }
+
   __device__ __forceinline__ void finish() {
     if constexpr (PASS == 2) {
       write_out(LONG ? (nsteps - 1) / (P.tile2 / 16) : 0);
     } else {
-      // Row sums of 4 blocks (16 quantities: block, row of the lane group) at a
-      // time; lane n of each row ends with quantity n and stores its partial.
-      static_assert(NBP == 4 || NBP == 8, "blocks in groups of four");
-      store_partials<0>();
-      if constexpr (NBP == 8) store_partials<4>();
+      store_tile(LONG ? (nsteps - 1) / (P.tile1 / 16) : 0);
     }
   }
 };

@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_P1B: {
       const Part part = st == ST_P1B ? PART_BASE : PART_ALL;
       const int n_rtg = part == PART_BASE ? P.n_rtg_base : P.n_rtg;
-      const int per_b = P.n_kt1 * n_rtg;
+      const int per_b = P.n_wt1 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
       score_tile<TT, D, G, 1, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, rem / n_rtg, rem % n_rtg,
                               reinterpret_cast<float*>(smem), part, 0u);
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_P1X: {
       int kt, rte;
       uint32_t hm;
-      const int b = ext_task(P, a, sg, P.n_kt1, blk, kt, rte, hm);
+      const int b = ext_task(P, a, sg, P.n_wt1, blk, kt, rte, hm);
       score_tile<TT, D, G, 1, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
                               reinterpret_cast<float*>(smem), PART_EXT, hm);
       break;
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_P2X: {
       int kt, rte;
       uint32_t hm;
-      const int b = ext_task(P, a, sg, P.n_kt2, blk, kt, rte, hm);
+      const int b = ext_task(P, a, sg, P.n_wt2, blk, kt, rte, hm);
       score_tile<TT, D, G, 2, LONG>(P, score_io(a, sg.layer, sg.slot, sg.step), b, kt, rte,
                               reinterpret_cast<float*>(smem), PART_EXT, hm);
       break;
@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_P2B: {
       const Part part = st == ST_P2B ? PART_BASE : PART_ALL;
       const int n_rtg = part == PART_BASE ? P.n_rtg_base : P.n_rtg;
-      const int per_b = P.n_kt2 * n_rtg;
+      const int per_b = P.n_wt2 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
       const ScoreIO io = score_io(a, sg.layer, sg.slot, sg.step);
       score_tile<TT, D, G, 2, LONG>(P, io, b, rem / n_rtg, rem % n_rtg, reinterpret_cast<float*>(smem),
