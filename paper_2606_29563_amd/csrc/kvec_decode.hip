@@ -136,54 +136,143 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial(DecArgs a) {
   const int32_t* ibp = ib ? ib : reinterpret_cast<const int32_t*>(kb);
   const int imax = ib ? a.B - 1 : 0;
   constexpr int kStep = kDecWaves * RPW;  // rows per round of the work-group
-  for (int base = r0; base < r1; base += kStep * kDecUnroll) {
-    uint4 ku[kDecUnroll], vu[kDecUnroll];
-    int iv[kDecUnroll];
-    bool live[kDecUnroll];
-    // issue every load of the unrolled rounds first, with no wait in between:
-    // the idx entries at clamped (in-bounds) positions, and the rows below
-    // n_ctx (all in bounds) whether or not idx masks them
+  // A round takes kDecUnroll rows per lane group, all their loads first: the
+  // idx entries at clamped (in-bounds) positions, and the rows below n_ctx (all
+  // in bounds) whether or not idx masks them; rows past the chunk load the
+  // chunk's last row (never used).
+  //
+  // bf16 rounds then take the dot products of all rows (independent lane-move
+  // chains) and rescale the state once.  Long caches are bound by the vector
+  // instructions between the rounds' loads: 16 sequences of 2085 rows (G 4,
+  // d 128) 37.9 us with a rescaling per row, 34.9 us so (3.9 TB/s).  Loading a
+  // round ahead takes 157 registers for 122 (three waves per SIMD for four):
+  // 35.5 us, and 14.7 for 13.9 us with 8 sequences of 600 rows; eight waves per
+  // work-group 38.0 us; the row tests after the dot products 132 registers and
+  // 37.9 us.  float32 rows have half the elements per lane to rescale: 16
+  // sequences of 2000 rows (G 2, d 64) 17.8 us row by row, 18.2 us at once.
+  if constexpr (sizeof(T) == 2) {
+    uint4 kn[kDecUnroll], vn[kDecUnroll];
+    int in[kDecUnroll];
+    auto issue = [&](int base) {
 #pragma unroll
-    for (int uu = 0; uu < kDecUnroll; ++uu) {
-      const int r = base + uu * kStep + w * RPW + grp;
-      // rows past the chunk load the chunk's last row (never used)
-      const int rl = min(r, r1 - 1);
-      iv[uu] = ibp[min(r, imax)];
-      live[uu] = r < r1;
-      ku[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
-      vu[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
-    }
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        const int r = base + uu * kStep + w * RPW + grp;
+        const int rl = min(r, r1 - 1);
+        in[uu] = ibp[min(r, imax)];
+        kn[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
+        vn[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
+      }
+    };
+    for (int base = r0; base < r1; base += kStep * kDecUnroll) {
+      issue(base);
+      uint4 ku[kDecUnroll], vu[kDecUnroll];
+      bool live[kDecUnroll];
 #pragma unroll
-    for (int uu = 0; uu < kDecUnroll; ++uu) {
-      const int r = base + uu * kStep + w * RPW + grp;
-      if (ib && r < a.B && iv[uu] < 0) live[uu] = false;
-      float kf[EPL], vf[EPL];
-      E::unpack(ku[uu], kf);
-      E::unpack(vu[uu], vf);
-      float x[G];
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        const int r = base + uu * kStep + w * RPW + grp;
+        live[uu] = r < r1 && !(ib && r < a.B && in[uu] < 0);
+        ku[uu] = kn[uu];
+        vu[uu] = vn[uu];
+      }
+      float x[kDecUnroll][G];
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float d = 0.f;
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        float kf[EPL];
+        E::unpack(ku[uu], kf);
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) d = fmaf(qv[g][e], kf[e], d);
-        x[g] = d;
+        for (int g = 0; g < G; ++g) {
+          float d = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) d = fmaf(qv[g][e], kf[e], d);
+          x[uu][g] = d;
+        }
       }
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        // every lane takes part in the lane moves, masked rows included
-        const float dsum = group_sum<LPR>(x[g]);
-        x[g] = live[uu] ? dsum * a.sc : -INFINITY;
-      }
+      for (int uu = 0; uu < kDecUnroll; ++uu)
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          // every lane takes part in the lane moves, masked rows included
+          const float dsum = group_sum<LPR>(x[uu][g]);
+          x[uu][g] = live[uu] ? dsum * a.sc : -INFINITY;
+        }
+      // online softmax, one rescaling per round; masked rows (x = -inf) leave
+      // the state as it is
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        // online softmax; a masked row (x = -inf) leaves the state as it is
-        const float mm = fmaxf(m[g], x[g]);
+        float mm = m[g];
+#pragma unroll
+        for (int uu = 0; uu < kDecUnroll; ++uu) mm = fmaxf(mm, x[uu][g]);
         const float f = m[g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - mm);
-        const float p = x[g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[g] - mm);
-        l[g] = l[g] * f + p;
+        l[g] *= f;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p, vf[e], acc[g][e] * f);
+        for (int uu = 0; uu < kDecUnroll; ++uu) {
+          x[uu][g] = x[uu][g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[uu][g] - mm);
+          l[g] += x[uu][g];
+        }
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[g][e] *= f;
         m[g] = mm;
+      }
+#pragma unroll
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        float vf[EPL];
+        E::unpack(vu[uu], vf);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(x[uu][g], vf[e], acc[g][e]);
+      }
+    }
+  } else {
+    for (int base = r0; base < r1; base += kStep * kDecUnroll) {
+      uint4 ku[kDecUnroll], vu[kDecUnroll];
+      int iv[kDecUnroll];
+      bool live[kDecUnroll];
+      // issue every load of the unrolled rounds first, with no wait in between:
+      // the idx entries at clamped (in-bounds) positions, and the rows below
+      // n_ctx (all in bounds) whether or not idx masks them
+#pragma unroll
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        const int r = base + uu * kStep + w * RPW + grp;
+        // rows past the chunk load the chunk's last row (never used)
+        const int rl = min(r, r1 - 1);
+        iv[uu] = ibp[min(r, imax)];
+        live[uu] = r < r1;
+        ku[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
+        vu[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
+      }
+#pragma unroll
+      for (int uu = 0; uu < kDecUnroll; ++uu) {
+        const int r = base + uu * kStep + w * RPW + grp;
+        if (ib && r < a.B && iv[uu] < 0) live[uu] = false;
+        float kf[EPL], vf[EPL];
+        E::unpack(ku[uu], kf);
+        E::unpack(vu[uu], vf);
+        float x[G];
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          float d = 0.f;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) d = fmaf(qv[g][e], kf[e], d);
+          x[g] = d;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          // every lane takes part in the lane moves, masked rows included
+          const float dsum = group_sum<LPR>(x[g]);
+          x[g] = live[uu] ? dsum * a.sc : -INFINITY;
+        }
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          // online softmax; a masked row (x = -inf) leaves the state as it is
+          const float mm = fmaxf(m[g], x[g]);
+          const float f = m[g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[g] - mm);
+          const float p = x[g] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[g] - mm);
+          l[g] = l[g] * f + p;
+#pragma unroll
+          for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(p, vf[e], acc[g][e] * f);
+          m[g] = mm;
+        }
       }
     }
   }
@@ -227,71 +316,79 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial(DecArgs a) {
 
 // Chunk states are read in batches of kDecBatch with every load of a batch in
 // flight at once (the chunks were written by other work-groups, on other
-// XCDs, so each read is a memory round trip): up to kDecBatch chunks in one
-// round trip, more in two passes (the maximum, then the rescaled sums).  Both
-// orders add the chunks in ascending order.
+// XCDs, so each read is a memory round trip).  Up to kDecBatch chunks are one
+// thread's single round trip; more go to kDecParts threads per element, each
+// a contiguous part, merged in ascending order through LDS: one round trip up
+// to 64 chunks instead of two a batch (33 chunks, one sequence of 2085 rows:
+// both launches 14.0 us before, 11.5 us now).
 constexpr int kDecBatch = 16;
+constexpr int kDecParts = 4;
 
-template <int D>
-__device__ __forceinline__ float combine_elem(const DecArgs& a, int b, int j, int e) {
-  const float* pp = a.part + ((int64_t)b * a.HQ + j) * a.S * (D + 2);
-  float m = -INFINITY, l = 0.f, av = 0.f;
-  if (a.S <= kDecBatch) {
+// Merge of the chunks s0 .. s1 - 1 into (m, l, av); ONE: they are one batch.
+template <int D, bool ONE>
+__device__ __forceinline__ void combine_part(const float* pp, int s0, int s1, int e, float& m, float& l, float& av) {
+  m = -INFINITY;
+  l = av = 0.f;
+  for (int c0 = s0; c0 < s1; c0 += kDecBatch) {
     float ms[kDecBatch], ls[kDecBatch], as[kDecBatch];
 #pragma unroll
     for (int i = 0; i < kDecBatch; ++i) {
-      const bool ok = i < a.S;
-      const float* q = pp + (int64_t)(ok ? i : 0) * (D + 2);
+      const bool ok = c0 + i < s1;
+      const float* q = pp + (int64_t)(ok ? c0 + i : s0) * (D + 2);
       ms[i] = ok ? q[0] : -INFINITY;
       ls[i] = q[1];
       as[i] = q[2 + e];
     }
+    float mm = m;
 #pragma unroll
-    for (int i = 0; i < kDecBatch; ++i) m = fmaxf(m, ms[i]);
-    if (m != -INFINITY) {
+    for (int i = 0; i < kDecBatch; ++i) mm = fmaxf(mm, ms[i]);
+    if (mm != -INFINITY) {
+      if (!ONE) {
+        const float f0 = __builtin_amdgcn_exp2f(m - mm);
+        l *= f0;
+        av *= f0;
+      }
 #pragma unroll
       for (int i = 0; i < kDecBatch; ++i) {
         // empty chunks (m = -inf) weigh exp2(-inf) = 0
-        const float f = __builtin_amdgcn_exp2f(ms[i] - m);
+        const float f = __builtin_amdgcn_exp2f(ms[i] - mm);
         l = fmaf(ls[i], f, l);
         av = fmaf(as[i], f, av);
       }
+      m = mm;
     }
-    return l > 0.f ? av / l : 0.f;
+    if (ONE) break;
   }
-  for (int s0 = 0; s0 < a.S; s0 += kDecBatch) {
-    float ms[kDecBatch];
+}
+
+template <int D, int PARTS>
+__global__ __launch_bounds__(D * PARTS) void decode_combine(DecArgs a) {
+  const int j = blockIdx.x, b = blockIdx.y, e = threadIdx.x % D;
+  // the same for a whole wave: the chunks' maxima and sums are scalar loads
+  const int part = PARTS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / D);
+  const float* pp = a.part + ((int64_t)b * a.HQ + j) * a.S * (D + 2);
+  const int per = (a.S + PARTS - 1) / PARTS;
+  float m, l, av;
+  combine_part<D, PARTS == 1>(pp, min(a.S, part * per), min(a.S, part * per + per), e, m, l, av);
+  if constexpr (PARTS > 1) {
+    __shared__ float st[PARTS][3][D];
+    st[part][0][e] = m;
+    st[part][1][e] = l;
+    st[part][2][e] = av;
+    __syncthreads();
+    if (part) return;
 #pragma unroll
-    for (int i = 0; i < kDecBatch; ++i) ms[i] = s0 + i < a.S ? pp[(s0 + i) * (D + 2)] : -INFINITY;
-#pragma unroll
-    for (int i = 0; i < kDecBatch; ++i) m = fmaxf(m, ms[i]);
+    for (int p = 1; p < PARTS; ++p) dec_merge(m, l, &av, st[p][0][e], st[p][1][e], &st[p][2][e], 1);
   }
-  if (m != -INFINITY) {
-    for (int s0 = 0; s0 < a.S; s0 += kDecBatch) {
-      float ms[kDecBatch], ls[kDecBatch], as[kDecBatch];
-#pragma unroll
-      for (int i = 0; i < kDecBatch; ++i) {
-        const bool ok = s0 + i < a.S;
-        const float* q = pp + (int64_t)(ok ? s0 + i : 0) * (D + 2);
-        ms[i] = ok ? q[0] : -INFINITY;
-        ls[i] = q[1];
-        as[i] = q[2 + e];
-      }
-#pragma unroll
-      for (int i = 0; i < kDecBatch; ++i) {
-        const float f = __builtin_amdgcn_exp2f(ms[i] - m);
-        l = fmaf(ls[i], f, l);
-        av = fmaf(as[i], f, av);
-      }
-    }
-  }
-  return l > 0.f ? av / l : 0.f;
+  a.out[((int64_t)b * a.HQ + j) * D + e] = l > 0.f ? av / l : 0.f;
 }
 
 template <int D>
-__global__ __launch_bounds__(D) void decode_combine(DecArgs a) {
-  const int j = blockIdx.x, b = blockIdx.y, e = threadIdx.x;
-  a.out[((int64_t)b * a.HQ + j) * D + e] = combine_elem<D>(a, b, j, e);
+void launch_combine(const DecArgs& a, int batch, hipStream_t s) {
+  if (a.S <= kDecBatch)
+    hipLaunchKernelGGL((decode_combine<D, 1>), dim3(a.HQ, batch), dim3(D), 0, s, a);
+  else
+    hipLaunchKernelGGL((decode_combine<D, kDecParts>), dim3(a.HQ, batch), dim3(D * kDecParts), 0, s, a);
 }
 
 typedef void (*DecFn)(DecArgs);
@@ -386,9 +483,9 @@ hipError_t run_decode(const Geometry& g, const void* q, const int64_t qs[2], con
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (P.D == 64)
-    hipLaunchKernelGGL(decode_combine<64>, dim3(P.HQ, P.batch), dim3(64), 0, s, a);
+    launch_combine<64>(a, P.batch, s);
   else
-    hipLaunchKernelGGL(decode_combine<128>, dim3(P.HQ, P.batch), dim3(128), 0, s, a);
+    launch_combine<128>(a, P.batch, s);
   return hipGetLastError();
 }
 

@@ -78,6 +78,15 @@ def test_decode_random_cache(gpu_lib, H, G, d, n, batch, dt):
     _check(kv, cfg, q, kc, vc)
 
 
+# chunk counts on both sides of the combine's single round trip (16) and its
+# four parts' (64), ragged last chunks and rounds
+@pytest.mark.parametrize("H,G,d,n,batch,dt", [(8, 4, 128, 16 * 64 + 1, 1, "bf16"), (8, 4, 128, 2085, 1, "bf16"),
+                                              (1, 2, 64, 21 * 64 - 5, 2, "f32"), (2, 7, 128, 64 * 64 + 33, 1, "bf16"),
+                                              (8, 3, 64, 1021, 16, "f32")])
+def test_decode_chunk_counts(gpu_lib, H, G, d, n, batch, dt):
+    test_decode_random_cache(gpu_lib, H, G, d, n, batch, dt)
+
+
 def test_decode_after_eviction_with_appended_rows(gpu_lib):
     """The compacted cache of a real eviction step (kvec_evict_model), copied
     into a larger buffer with 37 decode tokens appended after the B kept rows."""
