@@ -295,11 +295,11 @@ struct KeyRing {
 // normaliser recomputes that (row, tile) partial exactly.
 
 // LONG: a work-group takes P.sub key tiles in a row (model steps of many
-// work-groups): pass 1 stores the partials of one tile after the other, so the
-// sums are as short as with one tile each (the block references stay the first
-// tile's), pass 2 stages and writes out one tile after the other.  A variant of its own, in kernels of its own: the offsets
-// within the staged tile and the write-out inside the key loop cost every
-// other launch about 3%.
+// work-groups).  Pass 1 takes new block references and stores the partials
+// tile by tile, pass 2 stages and writes out tile by tile, so every tile's
+// results are the bytes that a work-group of its own gives.  In kernels of its
+// own: the offsets within the staged tile and the write-out inside the key loop
+// cost every other launch about 3%.
 template <class TT, int D, int G, int PASS, bool LONG>
 struct ScoreTile {
   using Tl = Tiling<G>;
@@ -611,6 +611,27 @@ struct ScoreTile {
     }
   }
 
+  // Pass 1: block references of the key tile that starts at step s, from its
+  // first 16 keys (fragment 0; step s computes its products again).  A row with
+  // any valid key in the tile sees the tile's first key, so a block is -inf only
+  // when none of its rows has a valid key here.
+  __device__ __forceinline__ void set_references(int s) {
+    mma_frag<0>();
+    const int t = ks + 16 * s + n;
+#pragma unroll
+    for (int bk = 0; bk < NB; ++bk) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const bool real = r_lo + (bk % RB) * 16 + 4 * c + i >= 0;  // not a padding row
+        const bool valid = real && t <= pos[bk % RB][i] && t < ke;
+        m = fmaxf(m, valid ? acc[bk][i] * P.sc : -INFINITY);
+      }
+      m = col_max4(row_max16(m));
+      mref[bk] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
+    }
+  }
+
   // Key steps in flight ahead of the one being read: step s + kAhead is
   // issued at step s into slot (s + kAhead) mod R, whose previous step was
   // read at step s + kAhead - R - 1 < s.
@@ -643,13 +664,15 @@ struct ScoreTile {
       if (LONG && F == 1 && (((s + 1) * 16) & (P.tile2 - 1)) == 0 && s + 1 < nsteps) write_out(s / (P.tile2 / 16));
     }
     if constexpr (PASS == 1 && LONG) {
-      // the partials of every tile but the last are stored here
+      // the partials of every tile but the last are stored here, and the next
+      // tile's references taken
       if (F == 1 && (((s + 1) * 16) & (P.tile1 - 1)) == 0 && s + 1 < nsteps) {
         store_tile(s / (P.tile1 / 16));
 #pragma unroll
         for (int bk = 0; bk < NB; ++bk)
 #pragma unroll
           for (int i = 0; i < 4; ++i) lsum[bk][i] = 0.f;
+        set_references(s + 1);
       }
     }
     if constexpr (NB >= 7) {
@@ -733,25 +756,7 @@ struct ScoreTile {
     }
     wait_vmem<(kAhead - 1) * KR::NI>();
     read_frag<0>(0);
-    if constexpr (PASS == 1) {
-      // Block references from the first 16 keys (recomputed by step 0).  A
-      // row with any valid key in this tile sees the tile's first key, so a
-      // block is -inf only when none of its rows has a valid key here.
-      mma_frag<0>();
-      const int t = ks + n;
-#pragma unroll
-      for (int bk = 0; bk < NB; ++bk) {
-        float m = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const bool real = r_lo + (bk % RB) * 16 + 4 * c + i >= 0;  // not a padding row
-          const bool valid = real && t <= pos[bk % RB][i] && t < ke;
-          m = fmaxf(m, valid ? acc[bk][i] * P.sc : -INFINITY);
-        }
-        m = col_max4(row_max16(m));
-        mref[bk] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
-      }
-    }
+    if constexpr (PASS == 1) set_references(0);
     // Only tiles that reach the causal edge, T or their own end need masks;
     // every other tile runs a loop without any masking code.
     const int last_t0 = ks + 16 * (nsteps - 1);

@@ -127,10 +127,14 @@ def test_long_score_work_groups(gpu_lib, case):
     # given normalisers: the same bytes as the per-layer call (one tile each)
     for a, b in zip(s.model(True, split=False), s.layers(True)):
         assert torch.equal(a, b)
-    # two passes: scores of the step against those of kvec_score.  The partial
-    # normalisers of 512 keys are scaled by another reference: each of the 32
-    # terms of a lane's sum may round differently, 32 float32 roundings (2e-6),
-    # and as many again in the exponentials' arguments (|x| up to 32)
+    # two passes: the step's scores are the bytes of kvec_score, whose
+    # work-groups take one key tile each
+    _same_scores(kv, s)
+
+
+def _same_scores(kv, s):
+    import torch
+    cfg, T, batch, H = s.cfg, s.cfg.seq_len, s.cfg.batch, s.cfg.n_kv_heads
     Tc = T - cfg.window
     p, pe = (torch.zeros((1, batch, H, Tc), device="cuda") for _ in range(2))
     imp = torch.zeros((1, batch, Tc), device="cuda")
@@ -139,6 +143,20 @@ def test_long_score_work_groups(gpu_lib, case):
     p1, pe1, imp1 = torch.empty_like(p[0]), torch.empty_like(p[0]), torch.empty_like(imp[0])
     kv.kvec_score(cfg, s.q[0], s.k[0], p1, pe1, imp1, s.ws)
     torch.cuda.synchronize()
-    assert torch.allclose(p[0], p1, rtol=4e-6, atol=0)
-    assert torch.allclose(pe[0], pe1, rtol=4e-6, atol=0)  # every head is in H_top (H <= 3)
-    assert torch.allclose(imp[0], imp1, rtol=4e-6, atol=0)
+    assert torch.equal(p[0], p1)
+    top = (htop[0][:, None] >> torch.arange(H, device="cuda")) & 1  # the others' rows stay zero
+    assert torch.equal(pe[0], pe1 * top[..., None])
+    assert torch.equal(imp[0], imp1)
+
+
+def test_long_score_work_groups_far_references(gpu_lib):
+    """Logits spread over more than the float32 exponent range: with the
+    references of another key tile, row sums lose terms or leave the range."""
+    import torch
+    kv = gpu_lib
+    cfg = _config(kv, 20011, 8, 4, 128, kv.KVEC_BF16, 12, layers=1, B=512)
+    s = Step(kv, cfg, torch.bfloat16, 13)
+    g = torch.Generator(device="cuda").manual_seed(14)
+    s.q *= 6
+    s.k *= 1 + 2 * (torch.rand(s.k.shape[:-1] + (1,), generator=g, device="cuda") < 0.01)
+    _same_scores(kv, s)
