@@ -611,13 +611,14 @@ struct ScoreTile {
     }
   }
 
-  // Pass 1: block references of the key tile that starts at step s, from its
-  // first 16 keys (fragment 0; step s computes its products again).  A row with
-  // any valid key in the tile sees the tile's first key, so a block is -inf only
-  // when none of its rows has a valid key here.
-  __device__ __forceinline__ void set_references(int s) {
+  // Pass 1, LONG: block references of the next key tile, which starts at key t0,
+  // from its first 16 keys (fragment 0; the next step computes their products
+  // again).  execute() has the same lines for the first tile: with this function
+  // called there, the compiler spills more in the kernels of eight row blocks at
+  // d = 128 (step of 4k tokens, one KV head 1186 against 1115 us; 2k, eight 1401 / 1346).
+  __device__ __forceinline__ void set_references(int t0) {
     mma_frag<0>();
-    const int t = ks + 16 * s + n;
+    const int t = t0 + n;
 #pragma unroll
     for (int bk = 0; bk < NB; ++bk) {
       float m = -INFINITY;
@@ -672,7 +673,7 @@ struct ScoreTile {
         for (int bk = 0; bk < NB; ++bk)
 #pragma unroll
           for (int i = 0; i < 4; ++i) lsum[bk][i] = 0.f;
-        set_references(s + 1);
+        set_references(ks + 16 * (s + 1));
       }
     }
     if constexpr (NB >= 7) {
@@ -756,7 +757,25 @@ struct ScoreTile {
     }
     wait_vmem<(kAhead - 1) * KR::NI>();
     read_frag<0>(0);
-    if constexpr (PASS == 1) set_references(0);
+    if constexpr (PASS == 1) {
+      // Block references from the first 16 keys (recomputed by step 0).  A
+      // row with any valid key in this tile sees the tile's first key, so a
+      // block is -inf only when none of its rows has a valid key here.
+      mma_frag<0>();
+      const int t = ks + n;
+#pragma unroll
+      for (int bk = 0; bk < NB; ++bk) {
+        float m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const bool real = r_lo + (bk % RB) * 16 + 4 * c + i >= 0;  // not a padding row
+          const bool valid = real && t <= pos[bk % RB][i] && t < ke;
+          m = fmaxf(m, valid ? acc[bk][i] * P.sc : -INFINITY);
+        }
+        m = col_max4(row_max16(m));
+        mref[bk] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));
+      }
+    }
     // Only tiles that reach the causal edge, T or their own end need masks;
     // every other tile runs a loop without any masking code.
     const int last_t0 = ks + 16 * (nsteps - 1);
