@@ -146,7 +146,7 @@ StepArgs base_args(const Geometry& g, char* ws, const Workspace& w) {
   a.P = g.p;
   a.w = w;
   a.ws = ws;
-  for (int s = 0; s < ST_N; ++s) a.seg[s] = Seg{-1, 0, 0, 0};
+  for (int s = 0; s < ST_N; ++s) a.seg[s] = Seg{-1, 0, 0, 0, 0};
   return a;
 }
 
@@ -178,9 +178,12 @@ void set_model(StepArgs& a, const ModelIO& m) {
   a.out_step = m.out_step;
 }
 
-hipError_t launch(const StepArgs& a, const Workspace& w, hipStream_t s) {
+hipError_t launch(StepArgs& a, const Workspace& w, hipStream_t s) {
   int total = 0;
-  for (int st = 0; st < ST_N; ++st) total += (a.seg[st].count + 7) & ~7;
+  for (int st = 0; st < ST_N; ++st) {
+    a.seg[st].first = total;
+    a.end[st] = total += (a.seg[st].count + 7) & ~7;
+  }
   if (total == 0) return hipSuccess;
   StepFn fn = pick(a.P);
   static_assert(sizeof(StepArgs) < 4096, "kernel argument block too large");
@@ -192,10 +195,10 @@ hipError_t launch(const StepArgs& a, const Workspace& w, hipStream_t s) {
 // call's n_steps x L layers leaves the stage out of the launch.
 void set_seg(StepArgs& a, int st, int v, int n_steps = 1) {
   if (v < 0 || v >= n_steps * a.P.L) {
-    a.seg[st] = Seg{-1, 0, 0, 0};
+    a.seg[st] = Seg{-1, 0, 0, 0, 0};
     return;
   }
-  a.seg[st] = Seg{v % a.P.L, v % kRing, seg_count(a.P, st), v / a.P.L};
+  a.seg[st] = Seg{v % a.P.L, v % kRing, seg_count(a.P, st), v / a.P.L, 0};
 }
 
 // Pass 1, row normalisers and pass 2 of one layer into ring slot 0 (pass 2
@@ -204,9 +207,9 @@ void set_seg(StepArgs& a, int st, int v, int n_steps = 1) {
 hipError_t score_stages(StepArgs a, const Workspace& w, hipStream_t s, int count_layer = -1) {
   const int order[3] = {ST_PASS1, ST_LSE, ST_PASS2};
   for (int i = a.lse ? 2 : 0; i < 3; ++i) {
-    for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0};
-    a.seg[order[i]] = Seg{0, 0, seg_count(a.P, order[i]), 0};
-    if (i == 2 && count_layer >= 0) a.seg[ST_CNTB] = Seg{count_layer, 0, seg_count(a.P, ST_CNTB), 0};
+    for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0, 0};
+    a.seg[order[i]] = Seg{0, 0, seg_count(a.P, order[i]), 0, 0};
+    if (i == 2 && count_layer >= 0) a.seg[ST_CNTB] = Seg{count_layer, 0, seg_count(a.P, ST_CNTB), 0, 0};
     const hipError_t e = launch(a, w, s);
     if (e != hipSuccess) return e;
   }
@@ -376,8 +379,8 @@ static hipError_t select_stages(const Geometry& g, int layer, const float* p_raw
   a.standalone_counts = 1;
   const int order[4] = {ST_CNTB, ST_POOL, ST_PREP, ST_SELAB};
   for (int i = p_raw ? 0 : 1; i < 4; ++i) {
-    for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0};
-    a.seg[order[i]] = Seg{layer, 0, seg_count(P, order[i]), 0};
+    for (int st = 0; st < ST_N; ++st) a.seg[st] = Seg{-1, 0, 0, 0, 0};
+    a.seg[order[i]] = Seg{layer, 0, seg_count(P, order[i]), 0, 0};
     const hipError_t e = launch(a, w, s);
     if (e != hipSuccess) return e;
   }
@@ -415,7 +418,7 @@ hipError_t run_compact(const Geometry& g, int n_layers, const ModelIO& m, hipStr
   a.idx_layer_stride = (int64_t)g.p.batch * g.p.H * g.p.B;
   a.out_layer = 1;
   for (int l = 0; l < n_layers; ++l) {
-    a.seg[ST_GATHER] = Seg{l, 0, seg_count(g.p, ST_GATHER), 0};
+    a.seg[ST_GATHER] = Seg{l, 0, seg_count(g.p, ST_GATHER), 0, 0};
     hipError_t e = launch(a, none, s);
     if (e != hipSuccess) return e;
   }

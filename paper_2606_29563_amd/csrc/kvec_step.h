@@ -31,6 +31,7 @@ struct Seg {
   int slot;   // ring slot of that layer's scratch
   int count;  // tasks of this stage in the launch (work-groups: rounded up to 8)
   int step;   // which of the call's independent steps the layer belongs to
+  int first;  // first work-group of the segment (set by the launch)
 };
 
 struct StepArgs {
@@ -61,6 +62,7 @@ struct StepArgs {
   // elements (words for bits) between consecutive steps of a multi-step call
   int64_t q_step, k_step, v_step, lse_step, bits_step, idx_step, out_step;
   Seg seg[ST_N];
+  int end[ST_N];  // work-groups of the launch up to and with each segment
 };
 
 __device__ __forceinline__ ScoreIO score_io(const StepArgs& a, int layer, int slot, int step = 0) {
@@ -220,15 +222,17 @@ template <class TT, int D, int G, bool LONG = false>
 __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
   extern __shared__ __align__(16) char smem[];
   const Problem P = a.P;
-  int blk = blockIdx.x;
+  // The segment of this work-group.  All ends are read at once: looked at one by
+  // one, each is a scalar load waited for before the next, so every stage in the
+  // list lengthened the launch for the stages after it (two stages more cost
+  // 1.3%).  Steps in the split pipeline, one by one / at once: 2k tokens 604 / 592
+  // us, 4k 640 / 618, 3k with four heads of d = 64 552 / 522, 32k 2052 / 2012.
   int st = 0;
-  for (; st < ST_N; ++st) {
-    const int n8 = (a.seg[st].count + 7) & ~7;
-    if (blk < n8) break;
-    blk -= n8;
-  }
+#pragma unroll
+  for (int i = 0; i < ST_N; ++i) st += (uint32_t)(a.end[i] - 1 - (int)blockIdx.x) >> 31;
   if (st >= ST_N) return;
   const Seg sg = a.seg[st];
+  int blk = (int)blockIdx.x - sg.first;
   {
     // XCD-aware remap: segments start at multiples of 8, so blk % 8 is the XCD
     const int n8 = (sg.count + 7) & ~7;
