@@ -32,9 +32,10 @@
 // their pool at j-3, prep at j-4, select A at j-5, select B and count at
 // j-6, gather at j-7.
 //
-// Small problems run the wide pipeline: pass 1, lse, pass 2 and pool of every
-// row and head at j .. j-3, prep at j-4, select A at j-5, select B and count
-// at j-6, gather at j-7 (two less with given normalisers).
+// Small problems run the wide pipeline: pass 1, lse, pass 2 and both pools of
+// every row and head (of the last-O rows alone without H_top heads) at j .. j-3,
+// prep at j-4, select A at j-5, select B and count at j-6, gather at j-7 (two
+// less with given normalisers).
 //
 // Work-group IDs are dispatched round-robin over the 8 XCDs, each with its
 // own L2.  Within a stage, consecutive tasks (e.g. the row tiles of one key
@@ -126,13 +127,17 @@ int seg_count(const Problem& P, int st) {
     case ST_P2B: return P.batch * P.n_wt2 * P.n_rtg_base;
     case ST_P2X: return ext_wgs(P, P.n_wt2);
     case ST_POOL:
-    case ST_POOLB: return P.batch * P.H * ((P.n_pool + kPoolPer - 1) / kPoolPer);
+    case ST_POOLB:
+    case ST_POOLE: return P.batch * P.H * ((P.n_pool + kPoolPer - 1) / kPoolPer);
     case ST_POOLX: return ext ? P.batch * P.delta_eff * ((P.n_pool + kPoolPer - 1) / kPoolPer) : 0;
     case ST_PREP: return P.batch * P.H * ((P.n_prep + kPrepPer - 1) / kPrepPer);
     case ST_GATHER: return P.batch * P.n_gather;
   }
   return 0;
 }
+
+// Work-groups of a stage in the grid (segments start at multiples of 8).
+int padded(const Problem& P, int st) { return (seg_count(P, st) + 7) & ~7; }
 
 StepFn pick(const Problem& P) {
   if (P.sub > 1) return P.D == 64 ? pick_g<BF16, 64, true>(P.G) : pick_g<BF16, 128, true>(P.G);
@@ -216,19 +221,43 @@ hipError_t score_stages(StepArgs a, const Workspace& w, hipStream_t s, int count
   return hipSuccess;
 }
 
-// Whether a model step scores all window rows of every head in one pass per
-// layer (the wide pipeline: four stages and launches shorter, two with given
-// normalisers) instead of the extended rows of the H_top heads four launches
-// later.  It scores more rows (all heads'), which costs nothing while a
-// launch's score work-groups leave compute units idle, so the line is at three
-// quarters of the 256 (the short stages take the rest).  Measured, us per step
-// split / wide: 128 work-groups (2k, 32 layers) 621 / 572, Qwen heads 16k
-// 1486 / 1377, given normalisers 4k 654 / 641 and 16k 1223 / 1172; 192 (12k,
-// given) 860 / 822; 16 (1k, float32, two layers) 262 / 158; but 256 (4k)
-// 635 / 968 and 256 (8k, 64 rows, given) 843 / 1425.
-bool wide_pays(const Problem& P, bool lse) {
-  const int64_t tiles = lse ? P.n_kt2 : P.n_kt1 + P.n_kt2;
-  return P.batch * tiles * P.n_rtg <= 192;
+constexpr int kCus = 256;
+
+// A stage of the wide pipeline: without H_top heads nothing needs the extended rows.
+int wide_stage(const Problem& P, int all, int base) { return P.delta_eff > 0 ? all : base; }
+
+// Whether a model step runs the wide pipeline: all window rows that some head
+// needs at once (four stages and launches shorter, two with given normalisers),
+// instead of the extended rows of the H_top heads four launches later.  It scores
+// more rows (all heads'), which costs nothing on compute units that would idle,
+// so the line depends on what else a launch holds; P over O' has pool work-groups
+// of its own, since one that pools both scores is the longest of a small launch.
+//
+// Keys in tiles of 128 (below 8k tokens) make score work-groups about twice as
+// long as the launch's others (selection, pool, prep, gather), which have to fit
+// beside them.  Longer ones (more keys, seven or eight row blocks, float32) leave
+// room for the others, but the more of them there are the longer they run, which
+// in a call of several steps, where only the last pays for the closing launches,
+// no longer pays.
+//
+// Measured, us per step split / wide (score work-groups, others).  8 KV heads, G
+// 4, d 128: 1k tokens 586 / 532 (64, 48), 2k 589 / 545 (128, 48), 3k 588 / 552
+// (192, 48), two of 1k 647 / 610 (128, 104); given normalisers 4k 638 / 611 (128,
+// 48), 12k 836 / 819 (188, 104), 24k 1240 / 1230 (188, 184), four of 1k 712 / 683
+// (128, 200).  d 64, 4k given 555 / 532.  Qwen heads 16k 2027 / 1878 (128).
+// float32 1k 1095 / 974.  Over the line: two of 1.5k 655 / 697 (192, 112), given
+// normalisers two of 3k 719 / 801 (192, 136), five of 1k 724 / 794 (160, 256), 4k
+// 611 / 872 (256).  Calls of six steps, given normalisers 16k 1102 / 1103 (128),
+// 12k 763 / 773 (188), 24k 1149 / 1193 (188).
+bool wide_pays(const Problem& P, bool lse, int n_steps) {
+  const int score = seg_count(P, wide_stage(P, ST_PASS2, ST_P2B)) +
+                    (lse ? 0 : seg_count(P, wide_stage(P, ST_PASS1, ST_P1B)));
+  if (score > kCus * 3 / 4) return false;
+  if (P.G >= 7 || P.esize == 4) return true;
+  if (P.tile1 > kTileMin) return n_steps == 1 || score <= kCus * 5 / 8;
+  int others = P.delta_eff > 0 ? padded(P, ST_POOLE) : 0;
+  for (int st : {ST_SELA, ST_SELECT, ST_POOLB, ST_PREP, ST_GATHER}) others += padded(P, st);
+  return score + others / 2 <= kCus * 15 / 16;
 }
 
 // Keys per score work-group of a model step.  About 10 of the 30-odd us that a
@@ -274,15 +303,16 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
   const int ns = m.n_steps > 0 ? m.n_steps : 1;
   // (a caller's events mark the launches of the split pipeline, and its score
   // outputs hold the extended rows' scores of the H_top heads only)
-  if (!ev && !m.sc_p && wide_pays(P, m.lse != nullptr)) {
+  if (!ev && !m.sc_p && wide_pays(P, m.lse != nullptr, ns)) {
     const int d = m.lse ? 2 : 0;  // stages that the given normalisers save
     for (int j = 0; j < ns * P.L + kPipeDepthWide - d; ++j) {
       if (!m.lse) {
-        set_seg(a, ST_PASS1, j, ns);
-        set_seg(a, ST_LSE, j - 1, ns);
+        set_seg(a, wide_stage(P, ST_PASS1, ST_P1B), j, ns);
+        set_seg(a, wide_stage(P, ST_LSE, ST_LSEB), j - 1, ns);
       }
-      set_seg(a, ST_PASS2, j - 2 + d, ns);
-      set_seg(a, ST_POOL, j - 3 + d, ns);
+      set_seg(a, wide_stage(P, ST_PASS2, ST_P2B), j - 2 + d, ns);
+      set_seg(a, ST_POOLB, j - 3 + d, ns);
+      if (P.delta_eff > 0) set_seg(a, ST_POOLE, j - 3 + d, ns);
       set_seg(a, ST_PREP, j - 4 + d, ns);
       set_seg(a, ST_SELA, j - 5 + d, ns);
       set_seg(a, ST_SELECT, j - 6 + d, ns);

@@ -16,13 +16,13 @@ namespace step {
 // *_X are the last-O and the extended-window halves of the layer pipeline;
 // the plain stages cover every row and head (per-layer entry points).  SELAB
 // and CNTB are the whole selection and the counts from the caller's bitmap of
-// a per-layer call.
+// a per-layer call.  POOLE pools P over O' of every head (wide pipeline).
 enum Stage {
   ST_SELECT = 0, ST_SELA, ST_SELAB, ST_COUNT, ST_CNTB,
   ST_PASS2, ST_P2B, ST_P2X,
   ST_PASS1, ST_P1B, ST_P1X,
   ST_LSE, ST_LSEB, ST_LSEX,
-  ST_POOL, ST_POOLB, ST_POOLX,
+  ST_POOL, ST_POOLB, ST_POOLX, ST_POOLE,
   ST_PREP, ST_GATHER, ST_N
 };
 
@@ -353,12 +353,13 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
                 smem, true, st == ST_POOL);
       break;
     }
-    case ST_POOLX: {
+    case ST_POOLX:
+    case ST_POOLE: {
       const int nt = (P.n_pool + kPoolPer - 1) / kPoolPer;
-      const int per_b = P.delta_eff * nt;
+      const int per_b = (st == ST_POOLX ? P.delta_eff : P.H) * nt;
       const int b = blk / per_b, rem = blk % per_b;
       const SelectIO io = select_io(a, sg.layer, sg.slot, sg.step);
-      const int h = nth_bit(htop_mask(P, io.stats, b), rem / nt);
+      const int h = st == ST_POOLX ? nth_bit(htop_mask(P, io.stats, b), rem / nt) : rem / nt;
       const int c0 = (rem % nt) * kPoolPer;
       if (h >= 0) task_pool(P, io, b, h, c0, min(P.n_pool, c0 + kPoolPer), smem, false, true);
       break;

@@ -58,6 +58,65 @@ def oracle_scores(w, layer: int, b: int, q=None, k=None):
     return p, pe, imp
 
 
+class StepPlan:
+    """The library's geometry and the rules by which a model step picks its
+    pipeline and its score work-groups, restated, so that a test can say which
+    route its case takes (a case that left its route would test nothing)."""
+
+    def __init__(self, cfg):
+        self.cfg = cfg
+        H, G, T, O, d = cfg.n_kv_heads, cfg.n_q_heads // cfg.n_kv_heads, cfg.seq_len, cfg.window, cfg.head_dim
+        self.es = es = 2 if cfg.dtype == 0 else 4
+        self.G, self.H, self.Wn, self.Tc = G, H, min(cfg.window_ext, T), T - O
+        self.WR = WR = 16 * (1 if G >= 4 else 4 // G)
+        self.delta = cfg.n_adjust_heads if self.Wn > O else 0
+        self.n_rt, self.n_rt_base = _up(self.Wn, WR), _up(O, WR)
+        self.nsum = 1 if O % WR == 0 else 2
+        tpw = 8 // H
+        self.n_rtg, self.n_rtg_base = _up(self.n_rt, tpw), _up(self.n_rt_base, tpw)
+        self.n_rt_x = self.n_rt - self.n_rt_base if self.delta else 0
+        tile = 512
+        while tile > 128 and tile * 32 > T:
+            tile //= 2
+        self.tile1, step = tile, 16 * d * es
+        ring = 8 * (4 if step <= 2048 else 3 if step <= 4096 else 1) * step
+
+        def slot(nh, sk, tile, exchange):
+            return ((1 if sk >= tile else 2) * WR * (sk + 4) if exchange else 0) + self.nsum * nh * tile + tile
+
+        def periods(tile):
+            sk, least = tile, 32 if tile == 512 else 16
+            while sk >= least:
+                yield sk
+                sk = 128 if sk == tile and tile > 128 else sk // 2
+
+        def fits(tile, sk):
+            ext = 8 * slot(1, sk, tile, False) if self.n_rt_x else 0
+            return ring + 4 * max(tpw * slot(H, sk, tile, H > 1), ext) <= 163840 - 1024
+
+        self.tile2, self.SK = next((t, sk) for t in (512, 256, 128) if t <= tile for sk in periods(t) if fits(t, sk))
+        self.n_kt1, self.n_kt2 = _up(T, self.tile1), _up(self.Tc, self.tile2)
+
+    def wide(self, given, n_steps=1):
+        """Whether a step runs the wide pipeline."""
+        c, b, H = self.cfg, self.cfg.batch, self.H
+        score = b * (self.n_kt2 + (0 if given else self.n_kt1)) * (self.n_rtg if self.delta else self.n_rtg_base)
+        if score > 192:
+            return False
+        if self.G >= 7 or self.es == 4:
+            return True
+        if self.tile1 > 128:
+            return n_steps == 1 or score <= 160
+        pool, prep = b * H * _up(self.Tc, 8 * 512), b * H * _up(self.Tc, 8 * 1024)
+        gather = b * _up(H * c.budget * c.head_dim * self.es // 16, 2048)
+        others = sum(_up(n, 8) * 8 for n in (b * H, b * H, pool, prep, gather) + ((pool,) if self.delta else ()))
+        return score + others // 2 <= 240
+
+
+def _up(n, m):
+    return -(-n // m)
+
+
 def rel_err(got: np.ndarray, ref: np.ndarray) -> float:
     got = np.asarray(got, np.float64)
     ref = np.asarray(ref, np.float64)

@@ -4,13 +4,15 @@ the per-layer entry points, which run the selection as one task.  Equality is
 exact: every route adds the same terms in the same order."""
 import pytest
 
+from kvec_testlib import StepPlan
+
 pytestmark = pytest.mark.gpu
 
 
-def _config(kv, T, H, G, d, dtype, batch=1, O=32, B=None, layers=4, beta=0.25):
+def _config(kv, T, H, G, d, dtype, batch=1, O=32, B=None, layers=4, beta=0.25, ext=None, adjust=3):
     return kv.Config(batch=batch, n_layers=layers, n_kv_heads=H, n_q_heads=H * G, head_dim=d, seq_len=T,
-                     window=O, window_ext=2 * O, budget=B or O + T // 8, pool_kernel=7,
-                     n_adjust_heads=min(3, H), lam=1.0, beta=beta, dtype=dtype)
+                     window=O, window_ext=ext or 2 * O, budget=B or O + T // 8, pool_kernel=7,
+                     n_adjust_heads=min(adjust, H), lam=1.0, beta=beta, dtype=dtype)
 
 
 class Step:
@@ -70,17 +72,23 @@ class Step:
         return o
 
 
-# (T, H, G, d, dtype, batch, O): both sides of the line of 192 score work-groups
-# (wide below it), ragged lengths, one and two row tiles per work-group, row
-# tiles that mix last-O and earlier rows
+# (T, H, G, d, dtype, batch, O, wide with two passes and with given normalisers):
+# both sides of the lines of the wide pipeline (score work-groups, what else a
+# launch holds), ragged lengths, key tiles of 128, 256 and 512, one and two row
+# tiles per work-group, row tiles that mix last-O and earlier rows
 CASES = [
-    (1024, 4, 2, 64, "f32", 1, 32),
-    (777, 8, 4, 128, "bf16", 2, 32),
-    (3071, 8, 4, 128, "bf16", 1, 32),
-    (3073, 8, 4, 128, "bf16", 1, 32),
-    (4096, 4, 7, 128, "bf16", 1, 32),
-    (2000, 8, 4, 128, "bf16", 1, 20),
-    (65, 2, 2, 64, "bf16", 3, 16),
+    (1024, 4, 2, 64, "f32", 1, 32, True, True),
+    (777, 8, 4, 128, "bf16", 2, 32, True, True),
+    (3071, 8, 4, 128, "bf16", 1, 32, True, True),
+    (3073, 8, 4, 128, "bf16", 1, 32, False, True),
+    (4096, 4, 7, 128, "bf16", 1, 32, True, True),
+    (4096, 8, 4, 64, "bf16", 1, 32, False, True),
+    (2048, 8, 4, 128, "bf16", 3, 32, False, False),
+    (12001, 2, 4, 128, "bf16", 1, 32, True, True),
+    (8200, 8, 1, 64, "bf16", 2, 40, False, True),
+    (16384 + 77, 2, 6, 128, "bf16", 1, 16, True, True),
+    (2000, 8, 4, 128, "bf16", 1, 20, True, True),
+    (65, 2, 2, 64, "bf16", 3, 16, True, True),
 ]
 
 
@@ -88,13 +96,33 @@ CASES = [
 @pytest.mark.parametrize("case", CASES, ids=lambda c: f"T{c[0]}-H{c[1]}-G{c[2]}-{c[4]}-b{c[5]}-O{c[6]}")
 def test_routes_agree(gpu_lib, case, given):
     import torch
-    T, H, G, d, dt, batch, O = case
+    T, H, G, d, dt, batch, O = case[:7]
     f32 = dt == "f32"
     cfg = _config(gpu_lib, T, H, G, d, gpu_lib.KVEC_F32 if f32 else gpu_lib.KVEC_BF16, batch, O)
+    assert StepPlan(cfg).wide(given) == case[8 if given else 7]
     s = Step(gpu_lib, cfg, torch.float32 if f32 else torch.bfloat16, T)
     want = s.model(given, split=True)
     for got in (s.model(given, split=False), s.layers(given)):
         for a, b in zip(got, want):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("ext,adjust", [(64, 0), (32, 3), (40, 1)], ids=["no-heads", "same-window", "mixed-tile"])
+@pytest.mark.parametrize("given", [False, True], ids=["two-pass", "given"])
+def test_routes_agree_few_extended_rows(gpu_lib, ext, adjust, given):
+    """Without H_top heads or without rows of their own the wide pipeline scores
+    the last-O rows only: the extended rows are not read (they hold NaN)."""
+    import torch
+    cfg = _config(gpu_lib, 1800, 8, 4, 128, gpu_lib.KVEC_BF16, ext=ext, adjust=adjust)
+    assert StepPlan(cfg).wide(given)
+    s = Step(gpu_lib, cfg, torch.bfloat16, ext)
+    if adjust == 0:
+        s.q[..., :32, :] = float("nan")
+        s.lse[..., :32] = float("nan")
+    want = s.model(given, split=True)
+    got = [s.model(given, split=False)] + ([s.layers(given)] if adjust else [])
+    for o in got:
+        for a, b in zip(o, want):
             assert torch.equal(a, b)
 
 
