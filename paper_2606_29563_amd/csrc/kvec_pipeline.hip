@@ -260,20 +260,31 @@ bool wide_pays(const Problem& P, bool lse, int n_steps) {
   return score + others / 2 <= kCus * 15 / 16;
 }
 
-// Keys per score work-group of a model step.  About 10 of the 30-odd us that a
-// work-group takes for 512 keys are fixed (code and first keys from memory,
-// queries, normalisers, write-out), so where a launch has many rounds of
-// work-groups, each takes two or four tiles in a row.  With few
-// rounds the coarser last round costs more than that saves.  Measured against
-// one tile each, by the score work-groups of a launch: up to 650 0.95 to 1.14
-// (mostly worse), 704 0.93 to 1.02, 860 to 1060 0.97, 1300 to 1410 0.89 to
-// 0.93, 2150 0.93 (four tiles 0.94), 2600 0.93 (four 0.91), 2800 0.90 (four
-// 0.88).
+// Key tiles per score work-group of a split-pipeline step.  About 10 of the 30-odd
+// us that a work-group takes for 512 keys are fixed (code and first keys from
+// memory, queries, normalisers, write-out), so where a launch has many rounds of
+// work-groups, each takes two or four tiles in a row; with few rounds the coarser
+// last round costs more than that saves.  The lines are in rounds of one
+// work-group per compute unit, over the passes of a launch: two tiles from 2.5
+// rounds (given normalisers: one pass) or 3.5 (two, which fill each other's last
+// round) on, four from 10 on.  Pass 1 with seven row blocks at d = 128 spills more
+// when it stores tile by tile, and with eight blocks four tiles never beat two.
+//
+// Measured, time against one tile by the work-groups of one tile in a launch; G 1 to
+// 8, d 64 and 128, one long prompt and batches.  Given normalisers: 500 to 600 0.92
+// to 1.20, 601 to 639 0.94 to 1.02, 640 to 700 0.93 to 1.01, 701 to 1000 0.84 to
+// 1.02, 1001 to 1500 0.70 to 0.97 (four 0.81 to 1.10), 1501 to 2300 0.88 to 0.92
+// (four 0.82 to 0.90), 2816 0.71 to 0.93 (four 0.71 to 0.89).  Two passes: 616 1.11,
+// 704 0.94 to 1.09, 750 to 895 0.98 to 1.01, 896 to 990 0.95 to 1.02, 1000 to 1300
+// 0.94 to 1.03, 1301 to 1600 0.89 to 0.98 (four 0.94 to 1.10), 1601 to 2300 0.93 to
+// 0.96 (four 0.95 to 1.05), 2500 to 2900 0.92 to 0.97 (four 0.89 to 0.94).  Two passes
+// at d = 128 with G 7 1.20 to 1.9 at any count, with G 8 0.83 at 2816 (four 0.94).
 void lengthen_tiles(Problem& P, bool lse) {
   if (P.esize != 2 || P.tile1 != kTileMax || P.tile2 != kTileMax) return;
-  const int64_t passes = lse ? 1 : 2;
-  const int64_t n = passes * ((int64_t)P.batch * P.n_kt1 * P.n_rtg_base + ext_wgs(P, P.n_kt1));
-  const int sub = n >= 10 * 256 ? 4 : n >= 11 * 64 ? 2 : 1;
+  auto pass = [&](int n_kt) { return (int64_t)P.batch * n_kt * P.n_rtg_base + ext_wgs(P, n_kt); };
+  const int64_t n = pass(P.n_kt2) + (lse ? 0 : pass(P.n_kt1));
+  int sub = n >= 10 * kCus ? 4 : 2 * n >= (lse ? 5 : 7) * kCus ? 2 : 1;
+  if (!lse && P.D == 128 && P.G >= 7) sub = P.G == 7 ? 1 : sub > 2 ? 2 : sub;
   P.sub = sub;
   P.n_wt1 = (P.n_kt1 + sub - 1) / sub;
   P.n_wt2 = (P.n_kt2 + sub - 1) / sub;

@@ -112,6 +112,21 @@ class StepPlan:
         others = sum(_up(n, 8) * 8 for n in (b * H, b * H, pool, prep, gather) + ((pool,) if self.delta else ()))
         return score + others // 2 <= 240
 
+    def tiles(self, given):
+        """Key tiles per score work-group of a step in the split pipeline."""
+        b, d = self.cfg.batch, self.cfg.head_dim
+        if self.es != 2 or self.tile1 != 512 or self.tile2 != 512:
+            return 1
+
+        def one_pass(n_kt):
+            return b * n_kt * self.n_rtg_base + _up(b * n_kt * self.delta * self.n_rt_x, 8)
+
+        n = one_pass(self.n_kt2) + (0 if given else one_pass(self.n_kt1))
+        sub = 4 if n >= 2560 else 2 if n >= (640 if given else 896) else 1
+        if not given and d == 128 and self.G >= 7:
+            sub = 1 if self.G == 7 else min(sub, 2)
+        return sub
+
 
 def _up(n, m):
     return -(-n // m)

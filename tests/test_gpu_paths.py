@@ -139,24 +139,46 @@ def test_routes_agree_all_members(gpu_lib, T):
             assert torch.equal(a, b)
 
 
-# batches whose launches hold enough score work-groups for two (704) and four
-# (2560) key tiles each; a ragged last tile, and row tiles of one and of two
-# 16-row blocks
-LONG = [(16384 + 77, 1, 4, 12), (16384 + 77, 2, 1, 24), (20011, 1, 4, 44)]
+# (T, H, G, d, batch, O, O', tiles with two passes and with given normalisers):
+# batches whose launches hold enough score work-groups for two and for four key
+# tiles each, ragged last tiles and last work-groups.  The heads' maxima are
+# exchanged over LDS with one buffer (periods of the whole tile: H 8 with G 4, 3
+# or 8, H 1 needs none) and with two (H 8 with O 20, G 1; H 4 with G 7; H 2 with
+# G 6); row tiles mix last-O and earlier rows where O is no multiple of their 16 to
+# 64 rows; seven and eight row blocks.  A tile of 256 keys (H 2, G 1) has none.
+LONG = [
+    (16384 + 77, 8, 4, 128, 10, 32, 64, 2, 2),
+    (16384 + 77, 8, 4, 128, 30, 32, 64, 4, 4),
+    (16384 + 77, 4, 7, 128, 12, 32, 64, 1, 2),
+    (16384 + 77, 4, 7, 128, 46, 32, 64, 1, 4),
+    (16384 + 77, 8, 8, 128, 6, 32, 64, 2, 1),
+    (16384 + 77, 1, 8, 128, 40, 32, 64, 2, 2),
+    (16900, 8, 1, 128, 30, 32, 64, 2, 2),
+    (16384 + 77, 8, 4, 128, 10, 20, 40, 2, 2),
+    (16384 + 77, 8, 3, 64, 10, 33, 71, 2, 2),
+    (16384 + 77, 2, 6, 128, 24, 32, 64, 2, 2),
+    (16384 + 77, 4, 2, 128, 16, 48, 120, 2, 2),
+    (16384 + 77, 1, 4, 64, 12, 32, 64, 2, 1),
+    (16384 + 77, 2, 1, 64, 24, 32, 64, 1, 1),
+    (20011, 1, 4, 64, 44, 32, 64, 4, 2),
+]
 
 
-@pytest.mark.parametrize("case", LONG, ids=lambda c: f"T{c[0]}-H{c[1]}-G{c[2]}-b{c[3]}")
+@pytest.mark.parametrize("case", LONG, ids=lambda c: f"T{c[0]}-H{c[1]}-G{c[2]}-d{c[3]}-b{c[4]}-O{c[5]}")
 def test_long_score_work_groups(gpu_lib, case):
+    """Steps and their scores are the bytes of the per-layer calls, whose score
+    work-groups take one key tile each."""
     import torch
     kv = gpu_lib
-    T, H, G, batch = case
-    cfg = _config(kv, T, H, G, 64, kv.KVEC_BF16, batch, layers=1, B=512)
+    T, H, G, d, batch, O, ext = case[:7]
+    cfg = _config(kv, T, H, G, d, kv.KVEC_BF16, batch, O, layers=1, B=512, ext=ext)
+    plan = StepPlan(cfg)
+    assert not plan.wide(False) and not plan.wide(True)
+    assert (plan.tiles(False), plan.tiles(True)) == case[7:]
     s = Step(kv, cfg, torch.bfloat16, 11)
-    # given normalisers: the same bytes as the per-layer call (one tile each)
-    for a, b in zip(s.model(True, split=False), s.layers(True)):
-        assert torch.equal(a, b)
-    # two passes: the step's scores are the bytes of kvec_score, whose
-    # work-groups take one key tile each
+    for given in (False, True):
+        for a, b in zip(s.model(given, split=False), s.layers(given)):
+            assert torch.equal(a, b)
     _same_scores(kv, s)
 
 
@@ -183,6 +205,7 @@ def test_long_score_work_groups_far_references(gpu_lib):
     import torch
     kv = gpu_lib
     cfg = _config(kv, 20011, 8, 4, 128, kv.KVEC_BF16, 12, layers=1, B=512)
+    assert StepPlan(cfg).tiles(False) == 4
     s = Step(kv, cfg, torch.bfloat16, 13)
     g = torch.Generator(device="cuda").manual_seed(14)
     s.q *= 6
