@@ -589,7 +589,7 @@ def main():
             ach = step_bytes / (ms_pipe * 1e-3) / 1e9
             steps_obj = {"entry": "kvec_evict_model_steps", "steps_per_call": n,
                          "what": "n back-to-back prefills evicted in one call: one layer pipeline "
-                                 "over their n x L layers (n x L + 11 fused launches)",
+                                 "over their n x L layers",
                          "inputs": "the resident prefill for every step (step stride 0); "
                                    "n distinct output sets",
                          "value": round(tokens / (ms_pipe * 1e-3), 1), "unit": "prefix tokens/s",

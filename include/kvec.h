@@ -231,8 +231,8 @@ kvec_status kvec_evict_model_scores(const kvec_config* cfg,
  * prefills (Sec. 4.1-4.2 for each, exactly as kvec_evict_model computes it),
  * run as one layer pipeline over their n_steps x L layers in order, so the
  * closing launches of one step overlap the opening launches of the next
- * (n_steps x L + 11 fused launches instead of n_steps x (L + 11)).  For
- * throughput across back-to-back prefills; every step's outputs equal those
+ * (n_steps x L + 11 fused launches instead of n_steps x (L + 11); 7 for 11 in
+ * small steps).  For throughput across back-to-back prefills; every step's outputs equal those
  * of a kvec_evict_model call on that step's inputs.
  *   n_steps      >= 1, n_steps x n_layers <= 2^20.
  *   q_win, k, v  device, as kvec_evict_model with one more leading stride:
@@ -265,8 +265,10 @@ kvec_status kvec_evict_model_lse_steps(const kvec_config* cfg, int32_t n_steps,
                                        void* v_out, void* ws, size_t ws_bytes,
                                        hipStream_t stream);
 
-/* Number of events kvec_evict_model records when given an event array
- * (n_layers + 12; 0 when T <= B), or -1 for an invalid configuration. */
+/* Number of events kvec_evict_model records when given an event array: one
+ * more than its launches (n_layers + 12, or n_layers + 8 where the step is small
+ * enough to score all window rows at once; 0 when T <= B), or -1 for an invalid
+ * configuration. */
 int32_t kvec_profile_points(const kvec_config* cfg);
 
 /* One layer, as kvec_evict_layer, with that layer's window-row normalisers
@@ -300,8 +302,8 @@ kvec_status kvec_evict_model_lse(const kvec_config* cfg,
                                  void* ws, size_t ws_bytes, hipStream_t stream,
                                  hipEvent_t* events);
 
-/* Number of events kvec_evict_model_lse records (n_layers + 8; 0 when
- * T <= B), or -1 for an invalid configuration. */
+/* Number of events kvec_evict_model_lse records (n_layers + 8, or n_layers + 6
+ * for small steps; 0 when T <= B), or -1 for an invalid configuration. */
 int32_t kvec_profile_points_lse(const kvec_config* cfg);
 
 /* Coverage C (Sec. 3.2) per sequence over layers 0..upto_layer:

@@ -584,7 +584,7 @@ kvec_status kvec_coverage(const kvec_config* cfg, const uint64_t* cover_bits, in
 int32_t kvec_profile_points(const kvec_config* cfg) {
   Geometry g;
   if (make_geometry(cfg, &g) != KVEC_OK) return -1;
-  return g.keep_all ? 0 : g.p.L + kPipeDepth + 1;
+  return g.keep_all ? 0 : step_launches(g.p, false) + 1;
 }
 
 kvec_status kvec_decode_workspace_size(const kvec_config* cfg, int32_t n_ctx, size_t* bytes) {
@@ -657,7 +657,7 @@ kvec_status kvec_decode_attention_noalloc(const kvec_config* cfg, const void* q,
 int32_t kvec_profile_points_lse(const kvec_config* cfg) {
   Geometry g;
   if (make_geometry(cfg, &g) != KVEC_OK) return -1;
-  return g.keep_all ? 0 : g.p.L + kPipeDepthLse + 1;
+  return g.keep_all ? 0 : step_launches(g.p, true) + 1;
 }
 
 const char* kvec_status_string(kvec_status s) {

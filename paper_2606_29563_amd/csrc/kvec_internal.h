@@ -126,6 +126,8 @@ struct ModelIO {
   int64_t q_step, k_step, v_step, lse_step, bits_step, idx_step, out_step;
 };
 
+// Launches of one model step (lse: with given normalisers).
+int step_launches(const Problem& P, bool lse);
 hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Workspace& w,
                      hipStream_t s, hipEvent_t* ev);
 hipError_t run_score(const Geometry& g, const void* q, const int64_t qs[3], const void* k,

@@ -297,7 +297,13 @@ hipError_t set_lds_limit(const Problem& P, const Workspace& w) {
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)w.lds_bytes);
 }
 
+int launches(const Problem& P, bool lse, int n_steps, bool wide) {
+  return n_steps * P.L + (wide ? kPipeDepthWide - (lse ? 2 : 0) : lse ? kPipeDepthLse : kPipeDepth);
+}
+
 }  // namespace
+
+int step_launches(const Problem& P, bool lse) { return launches(P, lse, 1, wide_pays(P, lse, 1)); }
 
 hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Workspace& w,
                      hipStream_t s, hipEvent_t* ev) {
@@ -312,11 +318,13 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
   // several steps: one pipeline over their n_steps x L layers in order (a
   // layer's selection chain only links layers of its own step)
   const int ns = m.n_steps > 0 ? m.n_steps : 1;
-  // (a caller's events mark the launches of the split pipeline, and its score
-  // outputs hold the extended rows' scores of the H_top heads only)
-  if (!ev && !m.sc_p && wide_pays(P, m.lse != nullptr, ns)) {
+  // (the caller's score outputs hold the extended rows' scores of the H_top heads
+  // only, as the split pipeline has them)
+  const bool wide = !m.sc_p && wide_pays(P, m.lse != nullptr, ns);
+  const int n_launch = launches(P, m.lse != nullptr, ns, wide);
+  if (wide) {
     const int d = m.lse ? 2 : 0;  // stages that the given normalisers save
-    for (int j = 0; j < ns * P.L + kPipeDepthWide - d; ++j) {
+    for (int j = 0; j < n_launch; ++j) {
       if (!m.lse) {
         set_seg(a, wide_stage(P, ST_PASS1, ST_P1B), j, ns);
         set_seg(a, wide_stage(P, ST_LSE, ST_LSEB), j - 1, ns);
@@ -329,8 +337,10 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
       set_seg(a, ST_SELECT, j - 6 + d, ns);
       set_seg(a, ST_COUNT, j - 6 + d, ns);
       set_seg(a, ST_GATHER, j - 7 + d, ns);
+      if (ev) (void)hipEventRecord(ev[j], s);
       if ((e = launch(a, w, s)) != hipSuccess) return e;
     }
+    if (ev) (void)hipEventRecord(ev[n_launch], s);
     return hipSuccess;
   }
   lengthen_tiles(a.P, m.lse != nullptr);
@@ -338,7 +348,6 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
   if (m.lse) {
     // The row normalisers come from the caller (the log-sum-exp of the
     // layer's prefill attention): no pass 1, a shorter pipeline.
-    const int n_launch = ns * P.L + kPipeDepthLse;
     for (int j = 0; j < n_launch; ++j) {
       set_seg(a, ST_P2B, j, ns);
       set_seg(a, ST_POOLB, j - 1, ns);
@@ -355,7 +364,6 @@ hipError_t run_model(const Geometry& g, const ModelIO& m, char* ws, const Worksp
     if (ev) (void)hipEventRecord(ev[n_launch], s);
     return hipSuccess;
   }
-  const int n_launch = ns * P.L + kPipeDepth;
   for (int j = 0; j < n_launch; ++j) {
     set_seg(a, ST_P1B, j, ns);
     set_seg(a, ST_LSEB, j - 1, ns);

@@ -215,6 +215,16 @@ def test_profile_points():
     assert kvec.kvec_profile_points_lse(_cfg(batch=0)) == -1
 
 
+def test_profile_points_of_small_steps():
+    """One event more than the step's launches, whichever pipeline it runs."""
+    small = dict(seq_len=2048, budget=128)
+    assert kvec.kvec_profile_points(_cfg(**small)) == 32 + 8
+    assert kvec.kvec_profile_points_lse(_cfg(**small)) == 32 + 6
+    # given normalisers halve the score work-groups: 4k is small with them only
+    assert kvec.kvec_profile_points(_cfg(seq_len=4096, budget=128)) == 32 + 12
+    assert kvec.kvec_profile_points_lse(_cfg(seq_len=4096, budget=128)) == 32 + 6
+
+
 def test_status_strings():
     for s in range(5):
         assert isinstance(kvec.status_string(s), str) and kvec.status_string(s)

@@ -1,7 +1,7 @@
 """The routes a model step can take give the same bytes: the wide pipeline
-(small problems), the split pipeline (the same call with profiling events), and
-the per-layer entry points, which run the selection as one task.  Equality is
-exact: every route adds the same terms in the same order."""
+(small problems), the split pipeline (larger ones, and every call that hands its
+scores out), and the per-layer entry points, which run the selection as one task.
+Equality is exact: every route adds the same terms in the same order."""
 import pytest
 
 from kvec_testlib import StepPlan
@@ -41,20 +41,36 @@ class Step:
                 torch.zeros(shape + (c.head_dim,), dtype=self.k.dtype, device="cuda"),
                 torch.zeros(shape + (c.head_dim,), dtype=self.k.dtype, device="cuda"))
 
-    def model(self, given, split):
+    def model(self, given, timed=False):
+        """The step as the library routes it; timed: with profiling events."""
         import torch
         o = self.outputs()
         ev = None
-        if split:
+        if timed:
             n = (self.kv.kvec_profile_points_lse if given else self.kv.kvec_profile_points)(self.cfg)
-            keep = [torch.cuda.Event() for _ in range(n)]
+            keep = [torch.cuda.Event(enable_timing=True) for _ in range(n)]
             for e in keep:
                 e.record()
+            torch.cuda.synchronize()
             ev = [e.cuda_event for e in keep]
         if given:
             self.kv.kvec_evict_model_lse(self.cfg, self.q, self.lse, self.k, self.v, *o, self.ws, events=ev)
         else:
             self.kv.kvec_evict_model(self.cfg, self.q, self.k, self.v, *o, self.ws, events=ev)
+        torch.cuda.synchronize()
+        if timed:  # every event was recorded, in order, with a launch in between
+            assert all(a.elapsed_time(b) > 0.001 for a, b in zip(keep, keep[1:]))
+        return o
+
+    def split(self):
+        """The step in the split pipeline, whatever its size."""
+        import torch
+        c, o = self.cfg, self.outputs()
+        Tc = c.seq_len - c.window
+        p, pe = (torch.zeros((c.n_layers, c.batch, c.n_kv_heads, Tc), device="cuda") for _ in range(2))
+        imp = torch.zeros((c.n_layers, c.batch, Tc), device="cuda")
+        htop = torch.zeros((c.n_layers, c.batch), dtype=torch.int32, device="cuda")
+        self.kv.kvec_evict_model_scores(c, self.q, self.k, self.v, *o, p, pe, imp, htop, self.ws)
         torch.cuda.synchronize()
         return o
 
@@ -101,8 +117,8 @@ def test_routes_agree(gpu_lib, case, given):
     cfg = _config(gpu_lib, T, H, G, d, gpu_lib.KVEC_F32 if f32 else gpu_lib.KVEC_BF16, batch, O)
     assert StepPlan(cfg).wide(given) == case[8 if given else 7]
     s = Step(gpu_lib, cfg, torch.float32 if f32 else torch.bfloat16, T)
-    want = s.model(given, split=True)
-    for got in (s.model(given, split=False), s.layers(given)):
+    want = s.layers(given)
+    for got in [s.model(given), s.model(given, timed=True)] + ([] if given else [s.split()]):
         for a, b in zip(got, want):
             assert torch.equal(a, b)
 
@@ -116,13 +132,12 @@ def test_routes_agree_few_extended_rows(gpu_lib, ext, adjust, given):
     cfg = _config(gpu_lib, 1800, 8, 4, 128, gpu_lib.KVEC_BF16, ext=ext, adjust=adjust)
     assert StepPlan(cfg).wide(given)
     s = Step(gpu_lib, cfg, torch.bfloat16, ext)
+    want = s.layers(given)
     if adjust == 0:
         s.q[..., :32, :] = float("nan")
         s.lse[..., :32] = float("nan")
-    want = s.model(given, split=True)
-    got = [s.model(given, split=False)] + ([s.layers(given)] if adjust else [])
-    for o in got:
-        for a, b in zip(o, want):
+    for got in [s.model(given)] + ([] if given else [s.split()]):
+        for a, b in zip(got, want):
             assert torch.equal(a, b)
 
 
@@ -133,8 +148,8 @@ def test_routes_agree_all_members(gpu_lib, T):
     import torch
     cfg = _config(gpu_lib, T, 2, 2, 64, gpu_lib.KVEC_BF16, layers=3)
     s = Step(gpu_lib, cfg, torch.bfloat16, 5, zero_q=True)
-    want = s.model(False, split=True)
-    for got in (s.model(False, split=False), s.layers(False)):
+    want = s.split()
+    for got in (s.model(False), s.layers(False)):
         for a, b in zip(got, want):
             assert torch.equal(a, b)
 
@@ -177,7 +192,7 @@ def test_long_score_work_groups(gpu_lib, case):
     assert (plan.tiles(False), plan.tiles(True)) == case[7:]
     s = Step(kv, cfg, torch.bfloat16, 11)
     for given in (False, True):
-        for a, b in zip(s.model(given, split=False), s.layers(given)):
+        for a, b in zip(s.model(given), s.layers(given)):
             assert torch.equal(a, b)
     _same_scores(kv, s)
 
