@@ -217,10 +217,14 @@ __device__ __forceinline__ int ext_task(const Problem& P, const StepArgs& a, con
   return b;
 }
 
-// LONG: the model steps whose pass-2 work-groups take several tiles (bf16).
+// LONG: the split pipeline with several key tiles per score work-group (bf16).
+// Nothing else is launched so: the stages of the per-layer calls and of the wide
+// pipeline are left out.
 template <class TT, int D, int G, bool LONG = false>
 __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
   extern __shared__ __align__(16) char smem[];
+  // two-pass steps of seven row blocks at d = 128 take one tile (lengthen_tiles)
+  constexpr bool kPass1 = !(LONG && D == 128 && G == 7);
   const Problem P = a.P;
   // The segment of this work-group.  All ends are read at once: looked at one by
   // one, each is a scalar load waited for before the next, so every stage in the
@@ -245,10 +249,11 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_SELAB: {
       const int b = blk / P.H, h = blk % P.H;
       task_select(P, select_io(a, sg.layer, sg.slot, sg.step), sg.layer, b, h, smem,
-                  st == ST_SELA ? SEL_A : st == ST_SELECT ? SEL_B : SEL_AB);
+                  st == ST_SELA ? SEL_A : LONG || st == ST_SELECT ? SEL_B : SEL_AB);
       break;
     }
     case ST_CNTB: {
+      if constexpr (LONG) break;
       const int parts = (P.words + kBitWords - 1) / kBitWords;
       task_counts_from_bits(P, a.bits, reinterpret_cast<uint8_t*>(a.ws + a.w.counts), sg.layer, blk / parts,
                             blk % parts);
@@ -274,7 +279,8 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     }
     case ST_PASS1:
     case ST_P1B: {
-      const Part part = st == ST_P1B ? PART_BASE : PART_ALL;
+      if constexpr (!kPass1) break;
+      const Part part = LONG || st == ST_P1B ? PART_BASE : PART_ALL;
       const int n_rtg = part == PART_BASE ? P.n_rtg_base : P.n_rtg;
       const int per_b = P.n_wt1 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
@@ -283,6 +289,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       break;
     }
     case ST_P1X: {
+      if constexpr (!kPass1) break;
       int kt, rte;
       uint32_t hm;
       const int b = ext_task(P, a, sg, P.n_wt1, blk, kt, rte, hm);
@@ -293,12 +300,13 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     case ST_LSE:
     case ST_LSEB:
     case ST_LSEX: {
+      if constexpr (!kPass1) break;
       const int per_b = lse_tasks_per_seq(P, st);
       const int b = blk / per_b;
       const int rb0 = base_row_lo(P);
       const uint32_t all = (1u << P.H) - 1u;
       const ScoreIO io = score_io(a, sg.layer, sg.slot, sg.step);
-      if (st == ST_LSE)
+      if (!LONG && st == ST_LSE)
         task_lse<TT, D, G>(P, io, b, blk % per_b, 0, P.Wn, all);
       else if (st == ST_LSEB)
         task_lse<TT, D, G>(P, io, b, blk % per_b, rb0, P.Wn - rb0, all);
@@ -317,7 +325,7 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
     }
     case ST_PASS2:
     case ST_P2B: {
-      const Part part = st == ST_P2B ? PART_BASE : PART_ALL;
+      const Part part = LONG || st == ST_P2B ? PART_BASE : PART_ALL;
       const int n_rtg = part == PART_BASE ? P.n_rtg_base : P.n_rtg;
       const int per_b = P.n_wt2 * n_rtg;
       const int b = blk / per_b, rem = blk % per_b;
@@ -350,16 +358,16 @@ __global__ __launch_bounds__(kThreads) void step_kernel(StepArgs a) {
       const int b = blk / per_b, rem = blk % per_b;
       const int c0 = (rem % nt) * kPoolPer;
       task_pool(P, select_io(a, sg.layer, sg.slot, sg.step), b, rem / nt, c0, min(P.n_pool, c0 + kPoolPer),
-                smem, true, st == ST_POOL);
+                smem, true, !LONG && st == ST_POOL);
       break;
     }
     case ST_POOLX:
     case ST_POOLE: {
       const int nt = (P.n_pool + kPoolPer - 1) / kPoolPer;
-      const int per_b = (st == ST_POOLX ? P.delta_eff : P.H) * nt;
+      const int per_b = (LONG || st == ST_POOLX ? P.delta_eff : P.H) * nt;
       const int b = blk / per_b, rem = blk % per_b;
       const SelectIO io = select_io(a, sg.layer, sg.slot, sg.step);
-      const int h = st == ST_POOLX ? nth_bit(htop_mask(P, io.stats, b), rem / nt) : rem / nt;
+      const int h = LONG || st == ST_POOLX ? nth_bit(htop_mask(P, io.stats, b), rem / nt) : rem / nt;
       const int c0 = (rem % nt) * kPoolPer;
       if (h >= 0) task_pool(P, io, b, h, c0, min(P.n_pool, c0 + kPoolPer), smem, false, true);
       break;

@@ -1,6 +1,7 @@
 // One (dtype, head_dim) pair of the step kernel, for every group size; built
 // once per pair with KVEC_INST_TT (BF16 or F32), KVEC_INST_D (64 or 128) and
-// KVEC_INST_LONG (true: the variant for long pass-2 work-groups, BF16 only).
+// KVEC_INST_LONG (true: the variant for several key tiles per score work-group,
+// BF16 only).
 #include "kvec_step.h"
 
 #if !defined(KVEC_INST_TT) || !defined(KVEC_INST_D) || !defined(KVEC_INST_LONG)
