@@ -136,43 +136,36 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial(DecArgs a) {
   const int32_t* ibp = ib ? ib : reinterpret_cast<const int32_t*>(kb);
   const int imax = ib ? a.B - 1 : 0;
   constexpr int kStep = kDecWaves * RPW;  // rows per round of the work-group
-  // A round takes kDecUnroll rows per lane group, all their loads first: the
-  // idx entries at clamped (in-bounds) positions, and the rows below n_ctx (all
-  // in bounds) whether or not idx masks them; rows past the chunk load the
-  // chunk's last row (never used).
-  //
-  // bf16 rounds then take the dot products of all rows (independent lane-move
-  // chains) and rescale the state once.  Long caches are bound by the vector
-  // instructions between the rounds' loads: 16 sequences of 2085 rows (G 4,
-  // d 128) 37.9 us with a rescaling per row, 34.9 us so (3.9 TB/s).  Loading a
-  // round ahead takes 157 registers for 122 (three waves per SIMD for four):
-  // 35.5 us, and 14.7 for 13.9 us with 8 sequences of 600 rows; eight waves per
-  // work-group 38.0 us; the row tests after the dot products 132 registers and
-  // 37.9 us.  float32 rows have half the elements per lane to rescale: 16
-  // sequences of 2000 rows (G 2, d 64) 17.8 us row by row, 18.2 us at once.
-  if constexpr (sizeof(T) == 2) {
-    uint4 kn[kDecUnroll], vn[kDecUnroll];
-    int in[kDecUnroll];
-    auto issue = [&](int base) {
+  for (int base = r0; base < r1; base += kStep * kDecUnroll) {
+    uint4 ku[kDecUnroll], vu[kDecUnroll];
+    int iv[kDecUnroll];
+    bool live[kDecUnroll];
+    // issue every load of a round (kDecUnroll rows per lane group) first, with no
+    // wait in between: the idx entries at clamped (in-bounds) positions, and the
+    // rows below n_ctx (all in bounds) whether or not idx masks them
+#pragma unroll
+    for (int uu = 0; uu < kDecUnroll; ++uu) {
+      const int r = base + uu * kStep + w * RPW + grp;
+      // rows past the chunk load the chunk's last row (never used)
+      const int rl = min(r, r1 - 1);
+      iv[uu] = ibp[min(r, imax)];
+      live[uu] = r < r1;
+      ku[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
+      vu[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
+    }
+    if constexpr (sizeof(T) == 2) {
+      // bf16: the dot products of all rows of the round (independent lane-move
+      // chains), then one rescaling of the online softmax state.  Long caches are
+      // bound by the vector instructions between the rounds' loads: 16 sequences of
+      // 2085 rows (G 4, d 128, cold buffers, from a graph) 37.0 us with a rescaling
+      // per row, 33.0 us so (4.1 TB/s), with idx 36.4 and 33.1; 8 sequences of 600
+      // rows 14.5 and 13.0.  Loading a round ahead takes one wave per SIMD (157
+      // registers) and was 6% slower with the 600 rows, eight waves per work-group
+      // 9% with the 2085.
 #pragma unroll
       for (int uu = 0; uu < kDecUnroll; ++uu) {
         const int r = base + uu * kStep + w * RPW + grp;
-        const int rl = min(r, r1 - 1);
-        in[uu] = ibp[min(r, imax)];
-        kn[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
-        vn[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
-      }
-    };
-    for (int base = r0; base < r1; base += kStep * kDecUnroll) {
-      issue(base);
-      uint4 ku[kDecUnroll], vu[kDecUnroll];
-      bool live[kDecUnroll];
-#pragma unroll
-      for (int uu = 0; uu < kDecUnroll; ++uu) {
-        const int r = base + uu * kStep + w * RPW + grp;
-        live[uu] = r < r1 && !(ib && r < a.B && in[uu] < 0);
-        ku[uu] = kn[uu];
-        vu[uu] = vn[uu];
+        if (ib && r < a.B && iv[uu] < 0) live[uu] = false;
       }
       float x[kDecUnroll][G];
 #pragma unroll
@@ -195,8 +188,7 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial(DecArgs a) {
           const float dsum = group_sum<LPR>(x[uu][g]);
           x[uu][g] = live[uu] ? dsum * a.sc : -INFINITY;
         }
-      // online softmax, one rescaling per round; masked rows (x = -inf) leave
-      // the state as it is
+      // masked rows (x = -inf) leave the state as it is
 #pragma unroll
       for (int g = 0; g < G; ++g) {
         float mm = m[g];
@@ -222,25 +214,9 @@ __global__ __launch_bounds__(kDecThreads) void decode_partial(DecArgs a) {
 #pragma unroll
           for (int e = 0; e < EPL; ++e) acc[g][e] = fmaf(x[uu][g], vf[e], acc[g][e]);
       }
-    }
-  } else {
-    for (int base = r0; base < r1; base += kStep * kDecUnroll) {
-      uint4 ku[kDecUnroll], vu[kDecUnroll];
-      int iv[kDecUnroll];
-      bool live[kDecUnroll];
-      // issue every load of the unrolled rounds first, with no wait in between:
-      // the idx entries at clamped (in-bounds) positions, and the rows below
-      // n_ctx (all in bounds) whether or not idx masks them
-#pragma unroll
-      for (int uu = 0; uu < kDecUnroll; ++uu) {
-        const int r = base + uu * kStep + w * RPW + grp;
-        // rows past the chunk load the chunk's last row (never used)
-        const int rl = min(r, r1 - 1);
-        iv[uu] = ibp[min(r, imax)];
-        live[uu] = r < r1;
-        ku[uu] = reinterpret_cast<const uint4*>(kb + (int64_t)rl * D * sizeof(T))[pc];
-        vu[uu] = reinterpret_cast<const uint4*>(vb + (int64_t)rl * D * sizeof(T))[pc];
-      }
+    } else {
+      // float32 rows have half the elements per lane to rescale: row by row (16
+      // sequences of 2000 rows, G 2, d 64, 17.8 us; at once 18.2)
 #pragma unroll
       for (int uu = 0; uu < kDecUnroll; ++uu) {
         const int r = base + uu * kStep + w * RPW + grp;
