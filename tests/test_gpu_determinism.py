@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 import synth
-from kvec_testlib import model_tensors, layer_inputs
+from kvec_testlib import StepPlan, model_tensors, layer_inputs
 
 pytestmark = pytest.mark.gpu
 
@@ -40,13 +40,15 @@ def _same(a, b, what):
     assert torch.equal(_bits(a), _bits(b)), f"{what} differs between two runs"
 
 
+@pytest.mark.parametrize("T,wide", [(3000, False), (1000, True)], ids=["split", "wide"])
 @pytest.mark.parametrize("lse", [False, True], ids=["two-pass", "given-lse"])
-def test_model_step_twice(gpu_lib, lse):
+def test_model_step_twice(gpu_lib, lse, T, wide):
     import torch
     kv = gpu_lib
-    w = _wl()
+    w = _wl(T=T)
     _say(f"[det] model step {w.name} L={w.n_layers} b={w.batch} lse={lse}")
     cfg = kv.Config.from_workload(w)
+    assert StepPlan(cfg).wide(lse) == wide
     ws = torch.empty(kv.kvec_workspace_size(cfg), dtype=torch.uint8, device="cuda")
     q, k, v = model_tensors(w)
     L, H, B, T, d = w.n_layers, w.n_kv_heads, w.budget, w.seq_len, w.head_dim

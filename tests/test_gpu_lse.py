@@ -9,7 +9,7 @@ import pytest
 
 import oracle as orc
 import synth
-from kvec_testlib import SCORE_RTOL, layer_inputs, oracle_scores, rel_err, to_device
+from kvec_testlib import SCORE_RTOL, StepPlan, layer_inputs, oracle_scores, rel_err, to_device
 from test_gpu_parity import SCORE_CASES, _e2e, _small
 
 pytestmark = pytest.mark.gpu
@@ -106,10 +106,12 @@ def test_full_llama8b_32k_lse_sampled_layers(gpu_lib):
     _e2e(gpu_lib, synth.workload(2), check_layers=[0, 1, 31], lse=True)
 
 
-def test_e2e_lse_window_equals_extended(gpu_lib):
-    """O' = O: no extended-window stages in the given-lse pipeline."""
-    _e2e(gpu_lib, _small("e2e-lse-wn-eq-o", 1800, 16, 16, 4, 2, 64, "bf16", B=120, layers=3),
-         lse=True)
+@pytest.mark.parametrize("T,batch,wide", [(1800, 1, True), (7000, 4, False)], ids=["wide", "split"])
+def test_e2e_lse_window_equals_extended(gpu_lib, T, batch, wide):
+    """O' = O: no extended-window stages in the given-lse pipelines."""
+    w = _small(f"e2e-lse-wn-eq-o-{T}", T, 16, 16, 4, 2, 64, "bf16", batch=batch, B=120, layers=3)
+    assert StepPlan(gpu_lib.Config.from_workload(w)).wide(True) == wide
+    _e2e(gpu_lib, w, lse=True)
 
 
 def test_e2e_lse_group7_entropy(gpu_lib):

@@ -141,6 +141,31 @@ def test_routes_agree_few_extended_rows(gpu_lib, ext, adjust, given):
             assert torch.equal(a, b)
 
 
+# (T, batch, layers, given): calls of several steps in the split pipeline, with
+# layer counts below and above its depth (several steps in one launch, ring slots
+# and count buffers reused across steps), and a prompt whose single step is wide
+STEPS = [(3100, 3, 4, False), (3100, 3, 13, False), (3100, 3, 4, True), (3100, 3, 13, True), (12001, 1, 3, True)]
+
+
+@pytest.mark.parametrize("T,batch,layers,given", STEPS)
+def test_steps_in_the_split_pipeline(gpu_lib, T, batch, layers, given):
+    import torch
+    kv, n = gpu_lib, 3
+    cfg = _config(kv, T, 8, 4, 128, kv.KVEC_BF16, batch, layers=layers)
+    assert not StepPlan(cfg).wide(given, n) and StepPlan(cfg).wide(given) == (batch == 1)
+    steps = [Step(kv, cfg, torch.bfloat16, 20 + i) for i in range(n)]
+    q, k, v, lse = (torch.stack([getattr(s, x) for s in steps]) for x in ("q", "k", "v", "lse"))
+    got = [torch.stack([o] * n) for o in steps[0].outputs()]
+    if given:
+        kv.kvec_evict_model_lse_steps(cfg, q, lse, k, v, *got, steps[0].ws)
+    else:
+        kv.kvec_evict_model_steps(cfg, q, k, v, *got, steps[0].ws)
+    torch.cuda.synchronize()
+    for i, s in enumerate(steps):
+        for a, b in zip(got, s.layers(given)):
+            assert torch.equal(a[i], b), f"step {i}"
+
+
 @pytest.mark.parametrize("T", [11500, 13000], ids=["members-in-lds", "members-spilled"])
 def test_routes_agree_all_members(gpu_lib, T):
     """Zero queries: all scores tie, so every token is a member; the longer
