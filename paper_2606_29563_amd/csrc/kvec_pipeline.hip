@@ -235,29 +235,33 @@ int wide_stage(const Problem& P, int all, int base) { return P.delta_eff > 0 ? a
 //
 // Keys in tiles of 128 (below 8k tokens) make score work-groups about twice as
 // long as the launch's others (selection, pool, prep, gather), which have to fit
-// beside them.  Longer ones (more keys, seven or eight row blocks, float32) leave
-// room for the others, but the more of them there are the longer they run, which
-// in a call of several steps, where only the last pays for the closing launches,
-// no longer pays.
+// beside them; seven or eight row blocks or float32 make them four times as long
+// at d = 64, and at d = 128 so long that the others do not matter.  Larger key tiles
+// leave room for the others too, but the more score work-groups there are the
+// longer they run, which in a call of several steps, where only the last pays for
+// the closing launches, no longer pays.
 //
 // Measured, us per step split / wide (score work-groups, others).  8 KV heads, G
 // 4, d 128: 1k tokens 586 / 532 (64, 48), 2k 589 / 545 (128, 48), 3k 588 / 552
 // (192, 48), two of 1k 647 / 610 (128, 104); given normalisers 4k 638 / 611 (128,
 // 48), 12k 836 / 819 (188, 104), 24k 1240 / 1230 (188, 184), four of 1k 712 / 683
-// (128, 200).  d 64, 4k given 555 / 532.  Qwen heads 16k 2027 / 1878 (128).
-// float32 1k 1095 / 974.  Over the line: two of 1.5k 655 / 697 (192, 112), given
-// normalisers two of 3k 719 / 801 (192, 136), five of 1k 724 / 794 (160, 256), 4k
-// 611 / 872 (256).  Calls of six steps, given normalisers 16k 1102 / 1103 (128),
-// 12k 763 / 773 (188), 24k 1149 / 1193 (188).
+// (128, 200).  d 64, 4k given 555 / 532.  Qwen heads 16k 2027 / 1878 (128); 24 of
+// 200 1212 / 1117 (192, 528).  float32, d 64: 1k 1095 / 974, 16 of 300 1273 / 1040
+// (96, 384), five of 1k 1215 / 1125 (160, 256).  Over the line: two of 1.5k 655 /
+// 697 (192, 112), given normalisers two of 3k 719 / 801 (192, 136), five of 1k 724 /
+// 794 (160, 256), 4k 611 / 872 (256); float32, d 64, six of 1k 1229 / 1277 (192,
+// 304).  Calls of six steps, given normalisers 16k 1102 / 1103 (128), 12k 763 / 773
+// (188), 24k 1149 / 1193 (188).
 bool wide_pays(const Problem& P, bool lse, int n_steps) {
   const int score = seg_count(P, wide_stage(P, ST_PASS2, ST_P2B)) +
                     (lse ? 0 : seg_count(P, wide_stage(P, ST_PASS1, ST_P1B)));
   if (score > kCus * 3 / 4) return false;
-  if (P.G >= 7 || P.esize == 4) return true;
-  if (P.tile1 > kTileMin) return n_steps == 1 || score <= kCus * 5 / 8;
+  const bool heavy = P.G >= 7 || P.esize == 4;
+  if (heavy && (P.D == 128 || score <= kCus * 3 / 8)) return true;
+  if (!heavy && P.tile1 > kTileMin) return n_steps == 1 || score <= kCus * 5 / 8;
   int others = P.delta_eff > 0 ? padded(P, ST_POOLE) : 0;
   for (int st : {ST_SELA, ST_SELECT, ST_POOLB, ST_PREP, ST_GATHER}) others += padded(P, st);
-  return score + others / 2 <= kCus * 15 / 16;
+  return score + others / (heavy ? 4 : 2) <= kCus * 15 / 16;
 }
 
 // Key tiles per score work-group of a split-pipeline step.  About 10 of the 30-odd

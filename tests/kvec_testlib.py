@@ -103,14 +103,15 @@ class StepPlan:
         score = b * (self.n_kt2 + (0 if given else self.n_kt1)) * (self.n_rtg if self.delta else self.n_rtg_base)
         if score > 192:
             return False
-        if self.G >= 7 or self.es == 4:
+        heavy = self.G >= 7 or self.es == 4
+        if heavy and (c.head_dim == 128 or score <= 96):
             return True
-        if self.tile1 > 128:
+        if not heavy and self.tile1 > 128:
             return n_steps == 1 or score <= 160
         pool, prep = b * H * _up(self.Tc, 8 * 512), b * H * _up(self.Tc, 8 * 1024)
         gather = b * _up(H * c.budget * c.head_dim * self.es // 16, 2048)
         others = sum(_up(n, 8) * 8 for n in (b * H, b * H, pool, prep, gather) + ((pool,) if self.delta else ()))
-        return score + others // 2 <= 240
+        return score + others // (4 if heavy else 2) <= 240
 
     def tiles(self, given):
         """Key tiles per score work-group of a step in the split pipeline."""

@@ -105,6 +105,10 @@ CASES = [
     (16384 + 77, 2, 6, 128, "bf16", 1, 16, True, True),
     (2000, 8, 4, 128, "bf16", 1, 20, True, True),
     (65, 2, 2, 64, "bf16", 3, 16, True, True),
+    (1000, 8, 8, 64, "bf16", 5, 32, False, True),
+    (1000, 8, 8, 64, "bf16", 6, 32, False, False),
+    (300, 4, 2, 64, "f32", 16, 32, True, True),
+    (1000, 8, 2, 64, "f32", 6, 32, False, True),
 ]
 
 
